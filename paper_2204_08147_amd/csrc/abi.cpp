@@ -463,8 +463,8 @@ extern "C" rdm_status rdm_apply(const rdm_hamiltonian* h, int32_t which, int32_t
   Seg sg{};
   sg.nbits = nbits;
   sg.n_row_tiles = g.n_row_tiles;
-  bind_apply(sg, op);
   sg.P = g.P;
+  bind_apply(sg, op);
   sg.S = g.S;
   sg.rpl = g.rpl;
   sg.C = n_cols;
@@ -496,8 +496,8 @@ extern "C" rdm_status rdm_apply(const rdm_hamiltonian* h, int32_t which, int32_t
                                       : launch_xz_pass<float>(pass, (Seg*)d, 1, L.xz, st, deep));
     RDM_HIP(precision == RDM_FP64 ? launch_apply<double>((Seg*)d, 1, L.apply, g.S, st)
                                   : launch_apply<float>((Seg*)d, 1, L.apply, g.S, st));
-    RDM_HIP(precision == RDM_FP64 ? launch_apply_wide<double>((Seg*)d, 1, L.wide, st)
-                                  : launch_apply_wide<float>((Seg*)d, 1, L.wide, st));
+    RDM_HIP(precision == RDM_FP64 ? launch_apply_wide<double>((Seg*)d, 1, L.wide, L.wsplit, st)
+                                  : launch_apply_wide<float>((Seg*)d, 1, L.wide, L.wsplit, st));
     RDM_HIP(hipStreamSynchronize(st));
     return RDM_OK;
   };

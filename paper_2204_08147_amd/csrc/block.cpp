@@ -97,8 +97,8 @@ rdm_status run_block(const BlockPlan& bp, const OpDevice* op_t, char* ws, char* 
     sg = Seg{};
     sg.nbits = bp.h->n;
     sg.n_row_tiles = bp.apply.n_row_tiles;
-    bind_apply(sg, op_t);
     sg.P = bp.apply.P;
+    bind_apply(sg, op_t);
     sg.S = 1;
     sg.rpl = 1;
     sg.C = bp.cpad;
@@ -150,7 +150,7 @@ rdm_status run_block(const BlockPlan& bp, const OpDevice* op_t, char* ws, char* 
     const Seg* sj = dsegs + (j - 1) % 3;
     if (tm) RDM_HIP(tm->apply.mark(st));
     RDM_HIP(launch_apply<T>(sj, 1, L.apply, 1, st));
-    RDM_HIP(launch_apply_wide<T>(sj, 1, L.wide, st));
+    RDM_HIP(launch_apply_wide<T>(sj, 1, L.wide, L.wsplit, st));
     if (op_t->xz)
       for (int pass = 4; pass <= 5; ++pass) RDM_HIP(launch_xz_pass<T>(pass, sj, 1, L.xz, st, deep));
     if (op_t->xz && op_t->xy)

@@ -52,7 +52,7 @@ struct OpTables {
   // the same two forms for bit-set tiles (kWideBits sites and more): tile bits
   // wbits; wide when products with the operator use them
   bool wide = false;
-  uint32_t wbits = 0;
+  uint32_t wbits = 0, wwin = 0;
   std::vector<uint32_t> w_flo, w_m;
   std::vector<double> w_cs, w_cd;
   std::vector<HopGroup> wgroups;
@@ -79,7 +79,8 @@ struct OpDevice {
   int ngroups = 0;
   // bit-set tile tables (wide operators)
   bool wide = false;
-  uint32_t wbits = 0;
+  uint32_t wbits = 0, wwin = 0;
+  void* wtab = nullptr;       // the allocation; the other three lie behind it
   void* whops = nullptr;
   void* wgroups = nullptr;
   void* wthin = nullptr;

@@ -69,10 +69,18 @@ constexpr int kFatGroup = 3;       // partner tiles read by at least this many h
 // others.  A hop with flip bits f reads the partner tile base ^ (f & ~B); B is
 // chosen per operator so that few distinct partner tiles remain.
 constexpr int kWideBits = 12;
-constexpr int kWideRows = 4;       // rows per lane
+constexpr int kWideRows = 8;       // rows per lane (register index q: the tile bits above the lanes')
 constexpr int kWideBlock = (1 << kWideBits) / kWideRows;  // lanes per workgroup
+constexpr int kWideParts = 4;      // workgroups per tile in launches of fewer than kWideSplit tiles
+constexpr int kWideSplit = 128;    // (two workgroups per CU, all of them resident)
+constexpr int kWideAhead = 4;      // hops read at a time there (the hop tables end with as many spare entries)
+constexpr int kWideWindowBits = 6; // tile bits inside the run of tiles an XCD works on at a time
 constexpr int kWideLowBits = 4;    // bits 0..3 are always in B
 constexpr int kWideFat = 2;        // partner tiles read by at least two hops go through LDS
+
+// Seg::wtab: the row bits of register index q, wave and lane of a workgroup
+// (tile index q * kWideBlock + wave * 64 + lane).
+enum { WT_Q = 0, WT_WAVE = WT_Q + kWideRows, WT_LANE = WT_WAVE + kWideBlock / 64, WT_COUNT = WT_LANE + 64 };
 
 // One off-diagonal term of H as the apply sees it: row idx couples to the
 // partner idx ^ f with coefficient c = (parity(idx & m) == 0) ? cs : cd.
@@ -88,9 +96,8 @@ struct alignas(16) GHop {
 // Hops sharing one partner tile (same fhi), stored contiguously in three kinds:
 // n0 with m = 0, n1 whose tested bits are all >= 6 (the coefficient is uniform
 // over a wave of 64 consecutive rows), n2 with a per-row coefficient.  In the
-// tables of bit-set tiles fhi = f & ~B, flo is the partner's tile index
-// offset (the bits of f & B compressed to B's positions), and the n1 hops
-// test no bit of B (the coefficient is uniform over the tile).
+// tables of bit-set tiles fhi = f & ~B, a group's hops are WHop entries, and
+// the n1 hops test no bit of B (the coefficient is uniform over the tile).
 struct HopGroup {
   uint32_t fhi;
   int32_t start;
@@ -98,6 +105,21 @@ struct HopGroup {
   int32_t tile_uniform;  // 1: only n1 hops, all tested bits >= 8, so every
                          // coefficient is uniform over a 256-row tile
   int32_t pad[2];
+};
+// One hop of the bit-set tile tables.  m: the row bits whose parity picks the
+// coefficient (the hop's own flip bits, or 0: always cs).  lmask: bit l is the
+// parity of m on the part of lane l (tile bits 0..5) of a wave; 0 when the
+// coefficient is uniform over a wave.  Staged hops: la = the flips of the
+// lane index in a workgroup (tile bits below the register bits), fq = those of
+// the register index.  Direct hops: la = the flips of the row index without
+// the register bits', fq as before.  more: the next hop of the table has the
+// same la (and belongs to the same group) and a larger fq.  Both tables end
+// with kWideAhead spare entries (the kernels read hops ahead).
+template <typename T>
+struct alignas(16) WHop {
+  uint64_t lmask;
+  uint32_t m, la, fq, more;
+  T cs, cd;
 };
 // Diagonal term: c * (1 - 2 * parity(idx & mask)).
 struct DiagTerm {
@@ -141,7 +163,11 @@ struct Seg {
   int32_t wide;        // 1: the apply takes bit-set tiles (hops / groups / thin and the
                        // counts above are then the bit-set tables)
   int32_t wp_base;     // first workgroup of this segment in a bit-set apply launch
+  int32_t wparts;      // partial sums per bit-set tile: kWideParts in segments of fewer than kWideSplit tiles
+  int32_t ws_base;     // first workgroup of this segment in a launch with kWideParts workgroups per tile
   uint32_t wbits;      // the row bits B that vary inside a bit-set tile
+  const void* wtab;    // row bits of a tile index: uint32 [WT_COUNT]
+  uint32_t wwin;       // the row bits that the low bits of a bit-set tile's index hold
   const void* dx;      // transform apply: D_X / 2^N in T (tile order above 20 bits)
   const void* dy;      // transform apply: D_Y / 2^N in T, same order (xy segments)
   void* Y;             // xy segments: one block of dim x cpad for the YY part
@@ -233,9 +259,11 @@ template <typename T>
 hipError_t launch_norm(const Seg* segs, int nseg, int ntiles, int slab, hipStream_t st);
 template <typename T>
 hipError_t launch_apply(const Seg* segs, int nseg, int ntiles, int slab, hipStream_t st);
-// the apply over the wide segments: ntiles = sum of 2^(nbits - kWideBits) * P
+// the apply over the wide segments: ntiles = sum of their 2^(nbits -
+// kWideBits) * P tiles with a workgroup each, or nsplit = kWideParts times as
+// many workgroups (the other one 0)
 template <typename T>
-hipError_t launch_apply_wide(const Seg* segs, int nseg, int ntiles, hipStream_t st);
+hipError_t launch_apply_wide(const Seg* segs, int nseg, int ntiles, int nsplit, hipStream_t st);
 // pass 0, 1 or 2 of the plain transform apply Y = H X (MODE_PLAIN segments
 // with xz = 1); passes 3 (once: X^ = W_lo X / 64 in place), 4 and 5 the same
 // product on blocks kept as X^, giving R = W_lo H X / 64; the strided pass

@@ -624,6 +624,20 @@ __global__ __launch_bounds__(kBlock) void k_apply(const Seg* __restrict__ segs, 
 // (the hops inside it) comes last, so the diagonal term and <u_j, r> read
 // the row's own value from LDS.  Hops whose partner tile no other hop reads
 // are gathered directly from memory.
+//
+// What bounds it: on dense operators (all pairs) the vector instructions and
+// the LDS reads of the hops, on sparse ones these and the partner tiles that
+// miss L2.  So a hop costs little beside its kWideRows multiply-adds per
+// column: its flips of the register index q are a compile-time permutation of
+// the registers read (a uniform branch), consecutive hops that flip the same
+// lane bits share their reads, and its coefficient is
+// one select per lane from a mask over the 64 lanes of a wave that the host
+// tabulates, the other bits' parity being uniform over the wave.  Measured
+// against one compare and select per row and per-row operand addresses on
+// 1024 lanes x 4 rows, tiles spread over the XCDs (us per launch, before ->
+// now): all-pairs XY on 16 sites x 1200 columns FP32 696 -> 518, now the LDS
+// reads' time; 16 sparse XXZ instances of 12..22 sites, FP32, 1718 -> 1458,
+// partner tiles that miss L2; 40 hops on 20 sites x 13 columns FP64 193 -> 130.
 // ---------------------------------------------------------------------------
 // the low bits of x deposited at the set bits of mask, lowest first
 __device__ __forceinline__ uint32_t deposit_bits(uint32_t x, uint32_t mask) {
@@ -637,44 +651,111 @@ struct WTile {
   int32_t seg;
   uint32_t base;   // row bits outside B
   int32_t panel;
-  int32_t tile;    // partial-sum row
+  int32_t tile;
+  int32_t part;    // which of the tile's PARTS workgroups
 };
 
 // The tile of this workgroup: binary search of blockIdx.x in the segments'
-// wp_base offsets, then panel-major inside the segment (the workgroups in
-// flight share one panel, whose partner tiles the memory-side cache holds).
-// Workgroups go round-robin to the 8 XCDs; inside a panel the k-th workgroup
-// of each XCD takes consecutive tiles, so partner tiles whose bases differ in
-// low tile bits are read through that XCD's L2.  A bijection on the panel's
-// 2^(N - kWideBits) tiles (a multiple of 8 from N = kWideBits + 3 on).
+// wp_base offsets, then panel-major inside the segment.  Workgroups go
+// round-robin to the 8 XCDs, and an XCD holds kXcdWindow = 64 of them at a
+// time (32 CUs, two each), whose tiles are as large as its L2: so each XCD
+// takes runs of 64 consecutive tiles, and the partner tiles of bases that
+// differ in the low tile bits (up to 18 bits: of the whole panel) are read
+// through its L2.  What is left behind the last 8 whole runs is split evenly.
+// A bijection on the segment's workgroups.
+constexpr int kXcdWindow = 64;
+template <int PARTS>
 __device__ __forceinline__ WTile wide_tile_of(const Seg* segs, int nseg) {
   const CONST_AS Seg* cs = (const CONST_AS Seg*)segs;
   const int b = (int)blockIdx.x;
   int lo = 0, hi = nseg - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (cs[mid].wp_base <= b) lo = mid;
+    if ((PARTS == 1 ? cs[mid].wp_base : cs[mid].ws_base) <= b) lo = mid;
     else hi = mid - 1;
   }
-  const int tb = cs[lo].nbits - kWideBits;
-  const int nt = 1 << tb;
-  const int lt = b - cs[lo].wp_base;
-  const int panel = lt >> tb;
-  int tile = lt & (nt - 1);
-  if (nt >= 8) tile = (tile & 7) * (nt >> 3) + (tile >> 3);
-  const uint32_t outside = ~cs[lo].wbits & ((1u << cs[lo].nbits) - 1u);
-  return WTile{lo, deposit_bits((uint32_t)tile, outside), panel, tile};
+  const int nt = PARTS << (cs[lo].nbits - kWideBits);
+  const int total = nt * cs[lo].P;
+  const int whole = total / (8 * kXcdWindow) * (8 * kXcdWindow);
+  int lt = b - (PARTS == 1 ? cs[lo].wp_base : cs[lo].ws_base);
+  const int rest = total - whole;
+  if (lt < whole) {
+    const int i = lt >> 3;
+    lt = ((i / kXcdWindow) * 8 + (lt & 7)) * kXcdWindow + i % kXcdWindow;
+  } else if (rest % 8 == 0) {
+    const int i = lt - whole;
+    lt = whole + (i & 7) * (rest >> 3) + (i >> 3);
+  }
+  const int panel = lt / nt, tile = lt % nt / PARTS, part = lt % PARTS;
+  // the low tile bits are the window's (chosen on the host), the others follow
+  const uint32_t win = cs[lo].wwin, outside = ~(cs[lo].wbits | win) & ((1u << cs[lo].nbits) - 1u);
+  return WTile{lo, deposit_bits((uint32_t)tile, win) | deposit_bits((uint32_t)tile >> __builtin_popcount(win), outside),
+               panel, tile, part};
 }
 
 template <typename T>
-__global__ __launch_bounds__(kWideBlock) void k_apply_wide(const Seg* __restrict__ segs, int nseg) {
+__device__ __forceinline__ WHop<T> load_hop(const CONST_AS WHop<T>* p) {
+  return WHop<T>{p->lmask, p->m, p->la, p->fq, p->more, p->cs, p->cd};
+}
+
+// acc += c x for one hop: row q of the lane reads x[q ^ FQ] (FQ: the register
+// bits it flips) with the coefficient of its class, c0 or c1 by the parity of
+// q & FQ (hops without a parity: c1 = c0).
+template <int FQ, int W, typename T, typename V>
+__device__ __forceinline__ void wide_hop(T (&acc)[kWideRows * W], const V (&x)[kWideRows], T c0, T c1) {
+#pragma unroll
+  for (int q = 0; q < kWideRows; ++q)
+#pragma unroll
+    for (int e = 0; e < W; ++e)
+      acc[q * W + e] = fma_s((__builtin_popcount(q & FQ) & 1) ? c1 : c0, x[q ^ FQ][e], acc[q * W + e]);
+}
+
+// The hops of one run (the same lane bits, ascending register bits; h is the
+// first, i its index), all on the operands x.  wbase: the row bits that the
+// wave's rows share.  Leaves h and i behind the run.
+template <int W, typename T, typename V>
+__device__ __forceinline__ void wide_run(T (&acc)[kWideRows * W], const V (&x)[kWideRows], const CONST_AS WHop<T>* hp,
+                                         int& i, WHop<T>& h, uint32_t wbase) {
+  bool more = true;
+  auto step = [&](auto fq) {
+    if (more && h.fq == (uint32_t)decltype(fq)::value) {
+      const bool odd = (__builtin_popcount(wbase & h.m) & 1u) != 0;
+      const T s0 = odd ? h.cd : h.cs, s1 = odd ? h.cs : h.cd;
+      const bool p = __builtin_amdgcn_inverse_ballot_w64(h.lmask);
+      const T c0 = p ? s1 : s0, c1 = p || !h.m ? s0 : s1;
+      more = h.more != 0u;
+      h = load_hop<T>(hp + ++i);       // a hop ahead
+      wide_hop<decltype(fq)::value, W>(acc, x, c0, c1);
+    }
+  };
+  static_assert(kWideRows == 8, "one step per flip of the register index");
+  step(std::integral_constant<int, 0>{});
+  step(std::integral_constant<int, 1>{});
+  step(std::integral_constant<int, 2>{});
+  step(std::integral_constant<int, 3>{});
+  step(std::integral_constant<int, 4>{});
+  step(std::integral_constant<int, 5>{});
+  step(std::integral_constant<int, 6>{});
+  step(std::integral_constant<int, 7>{});
+}
+
+// R = kWideRows: a workgroup computes every row of its tile.  R = kWideRows /
+// kWideParts: kWideParts workgroups share a tile, each staging all of it but
+// computing the rows of R register indexes q = q0 .. q0 + R - 1 only (launches
+// whose tiles would leave most CUs idle: the all-pairs XXZ operator on 16
+// sites with 4 FP64 columns, 32 tiles, went from 46.6 to 30.7 us).  The hops of
+// every row keep their order, and the segments this can happen to
+// (Seg::wparts) have one partial sum per part either way, so the results are
+// the same in both.
+template <typename T, int R>
+__global__ __launch_bounds__(kWideBlock, 4) void k_apply_wide(const Seg* __restrict__ segs, int nseg) {
   using V = typename PanelT<T>::V;
   constexpr int W = PanelT<T>::W;
-  constexpr int R = kWideRows;
+  constexpr int Q = kWideRows;
   constexpr int NW = kWideBlock / 64;
   __shared__ V tl[1 << kWideBits];
-  __shared__ double lds[NW * W];
-  const WTile t = wide_tile_of(segs, nseg);
+  __shared__ double lds[kWideParts * NW * W];
+  const WTile t = wide_tile_of<Q / R>(segs, nseg);
   const CONST_AS CSeg& sg = cseg(segs, t.seg);
   const bool plain = sg.mode == MODE_PLAIN;
   int j = 1;
@@ -688,195 +769,181 @@ __global__ __launch_bounds__(kWideBlock) void k_apply_wide(const Seg* __restrict
   const V* uprev = (!plain && j > 1) ? (const V*)slot_ptr<T>(sg, j - 1) + (uint64_t)t.panel * pstride
                                      : nullptr;
   V* out = (V*)sg.R + (uint64_t)t.panel * pstride;
-  const CONST_AS GHop<T>* hp = (const CONST_AS GHop<T>*)sg.hops;
+  const CONST_AS WHop<T>* hp = (const CONST_AS WHop<T>*)sg.hops;
   const CONST_AS HopGroup* gr = (const CONST_AS HopGroup*)sg.groups;
   const int ng = sg.ngroups;
   const T* dg = (const T*)sg.diag;
   const bool dots = sg.mode == MODE_LANCZOS;
   const CONST_AS double* st = (const CONST_AS double*)sg.st;
 
-  const uint32_t B = sg.wbits;
   const uint32_t lane = threadIdx.x;
-  const uint32_t lrow = t.base | deposit_bits(lane, B);
-  // row q of the lane = lrow | dep[q]; dep[q] is uniform, so a per-row
-  // coefficient parity(row & m) is parity(lrow & m) (per lane, once per hop)
-  // flipped by the uniform parity(dep[q] & m)
-  uint32_t dep[R], row[R];
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t q0 = R == Q ? 0u : (uint32_t)t.part * R;
+  // row q of the lane = lrow | dep[q]; wbase: the bits the wave's rows share
+  // at q = q0 (uniform).  The deposits come from a table of the host's: the
+  // loop over the bits of B would cost each workgroup about a microsecond
+  const CONST_AS uint32_t* tab = (const CONST_AS uint32_t*)sg.wtab;
+  uint32_t dep[Q];
 #pragma unroll
-  for (int q = 0; q < R; ++q) {
-    dep[q] = deposit_bits((uint32_t)(q * kWideBlock), B);
-    row[q] = lrow | dep[q];
-  }
-  auto row_coefs = [&](uint32_t m, T cs, T cd, T (&c)[R]) {
-    const bool p0 = __builtin_popcount(lrow & m) & 1u;
-    const T ca = p0 ? cd : cs, cb = p0 ? cs : cd;
+  for (int q = 0; q < Q; ++q) dep[q] = tab[WT_Q + q];
+  const uint32_t depq0 = R == Q ? 0u : tab[WT_Q + q0];
+  const uint32_t dwave = t.base | tab[WT_WAVE + wave];
+  const uint32_t wbase = dwave | depq0;
+  const uint32_t lrow = dwave | ldg_s((const uint32_t*)sg.wtab + WT_LANE, lane & 63u);
+  uint32_t row[R];               // the rows the lane computes
 #pragma unroll
-    for (int q = 0; q < R; ++q) c[q] = (__builtin_popcount(dep[q] & m) & 1u) ? cb : ca;
+  for (int r = 0; r < R; ++r) row[r] = lrow | (R == Q ? dep[r] : depq0 | dep[r]);
+
+  T acc[R * W];
+  V nx[Q], x[R];
+#pragma unroll
+  for (int i = 0; i < R * W; ++i) acc[i] = T(0);
+  // one hop on R < Q rows (row r reads the operand of its own partner)
+  auto hop_part = [&](const WHop<T>& h, const V (&xr)[R]) {
+    const bool odd = (__builtin_popcount(wbase & h.m) & 1u) != 0;
+    const T s0 = odd ? h.cd : h.cs, s1 = odd ? h.cs : h.cd;
+    const bool p = __builtin_amdgcn_inverse_ballot_w64(h.lmask);
+    const T ca = p ? s1 : s0, cb = p ? s0 : s1;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const T c = h.m && (__builtin_popcount(h.fq & (uint32_t)r) & 1u) ? cb : ca;
+#pragma unroll
+      for (int e = 0; e < W; ++e) acc[r * W + e] = fma_s(c, xr[r][e], acc[r * W + e]);
+    }
   };
 
-  // next partner group (1 .. ng-1) that contributes to this tile: a
-  // tile-uniform group whose coefficients all vanish here is skipped (no
-  // load, no barrier); ng stands for the own tile (group 0), staged last so
-  // that its values are still in LDS for the diagonal and the dot products
-  auto next_active = [&](int g) -> int {
-    for (; g < ng; ++g) {
-      if (!gr[g].tile_uniform) return g;
-      const int h0 = gr[g].start, n1 = gr[g].n1;
-      for (int h = h0; h < h0 + n1; ++h) {
-        const T c = (__builtin_popcount(t.base & hp[h].m) & 1u) ? hp[h].cd : hp[h].cs;
-        if (c != T(0)) return g;
-      }
-    }
-    return ng;
+  // the next partner tile, on its way to LDS: groups 1 .. ng - 1, then the own
+  int g = 1 < ng ? 1 : 0;
+  auto fetch = [&](int i) {
+    const uint32_t f = gr[i].fhi;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) nx[q] = ldg(ub, (lrow ^ f) ^ dep[q]);
   };
+  fetch(g);
 
-  V acc[R], nx[R];
-#pragma unroll
-  for (int q = 0; q < R; ++q)
-#pragma unroll
-    for (int e = 0; e < W; ++e) acc[q][e] = T(0);
-  int g = next_active(1);
+  // hops whose partner tile no other hop reads: gathered directly, while the
+  // first staged tile is on its way
   {
-    const uint32_t f = g < ng ? gr[g].fhi : 0u;
+    const CONST_AS WHop<T>* th = (const CONST_AS WHop<T>*)sg.thin;
+    const int nthin = sg.nt0 + sg.nt1 + sg.nt2;
+    if constexpr (R == Q) {
+      WHop<T> h = load_hop<T>(th);
+      int i = 0;
+      const uint32_t B = sg.wbits;
+      auto skip = [&]() {              // hops that are zero on every row of the tile: nothing to read
+        while (i < nthin && (h.m & B) == 0u && ((__builtin_popcount(t.base & h.m) & 1u) ? h.cd : h.cs) == T(0))
+          h = load_hop<T>(th + ++i);
+      };
+      for (skip(); i < nthin; skip()) {
+        const uint32_t rr = lrow ^ h.la;
 #pragma unroll
-    for (int q = 0; q < R; ++q) nx[q] = ldg(ub, row[q] ^ f);
-  }
-
-  // hops whose partner tile no other hop reads: gathered directly, two hops
-  // (2R loads) in flight, while the first staged tile is on its way
-  {
-    const CONST_AS GHop<T>* th = (const CONST_AS GHop<T>*)sg.thin;
-    const int e0 = sg.nt0, e1 = e0 + sg.nt1, e2 = e1 + sg.nt2;
-    int h = 0;
-    for (; h < e0; ++h) {
-      const uint32_t f = th[h].flo;
-      const T c = th[h].cs;
-      V x[R];
-#pragma unroll
-      for (int q = 0; q < R; ++q) x[q] = ldg(ub, row[q] ^ f);
-#pragma unroll
-      for (int q = 0; q < R; ++q) acc[q] += c * x[q];
-    }
-    for (; h < e1; ++h) {
-      const T c = (__builtin_popcount(t.base & th[h].m) & 1u) ? th[h].cd : th[h].cs;
-      if (c == T(0)) continue;
-      const uint32_t f = th[h].flo;
-      V x[R];
-#pragma unroll
-      for (int q = 0; q < R; ++q) x[q] = ldg(ub, row[q] ^ f);
-#pragma unroll
-      for (int q = 0; q < R; ++q) acc[q] += c * x[q];
-    }
-    for (; h + 2 <= e2; h += 2) {
-      const uint32_t f0 = th[h].flo, f1 = th[h + 1].flo;
-      V x0[R], x1[R];
-#pragma unroll
-      for (int q = 0; q < R; ++q) {
-        x0[q] = ldg(ub, row[q] ^ f0);
-        x1[q] = ldg(ub, row[q] ^ f1);
+        for (int q = 0; q < Q; ++q) x[q] = ldg(ub, rr ^ dep[q]);
+        wide_run<W, T>(acc, x, th, i, h, wbase);
       }
-      T c0[R], c1[R];
-      row_coefs(th[h].m, th[h].cs, th[h].cd, c0);
-      row_coefs(th[h + 1].m, th[h + 1].cs, th[h + 1].cd, c1);
+    } else {
+      // kWideAhead at a time (the spare entries read the row itself)
+      for (int i = 0; i < nthin; i += kWideAhead) {
+        WHop<T> h[kWideAhead];
+        V xa[kWideAhead][R];
 #pragma unroll
-      for (int q = 0; q < R; ++q) {
-        acc[q] += c0[q] * x0[q];
-        acc[q] += c1[q] * x1[q];
+        for (int u = 0; u < kWideAhead; ++u) h[u] = load_hop<T>(th + i + u);
+#pragma unroll
+        for (int u = 0; u < kWideAhead; ++u)
+#pragma unroll
+          for (int r = 0; r < R; ++r) xa[u][r] = ldg(ub, row[r] ^ h[u].la ^ tab[WT_Q + h[u].fq]);
+#pragma unroll
+        for (int u = 0; u < kWideAhead; ++u)
+          if (i + u < nthin) hop_part(h[u], xa[u]);
       }
-    }
-    if (h < e2) {
-      const uint32_t f = th[h].flo;
-      V x[R];
-#pragma unroll
-      for (int q = 0; q < R; ++q) x[q] = ldg(ub, row[q] ^ f);
-      T c[R];
-      row_coefs(th[h].m, th[h].cs, th[h].cd, c);
-#pragma unroll
-      for (int q = 0; q < R; ++q) acc[q] += c[q] * x[q];
     }
   }
 
   for (;;) {
-    const int cur = g < ng ? g : 0;
-    const int gn = g < ng ? next_active(g + 1) : -1;
     __syncthreads();             // the previous group's reads of tl are done
 #pragma unroll
-    for (int q = 0; q < R; ++q) tl[lane + q * kWideBlock] = nx[q];
+    for (int q = 0; q < Q; ++q) tl[lane + q * kWideBlock] = nx[q];
     __syncthreads();
-    if (gn >= 0) {
-      const uint32_t f = gn < ng ? gr[gn].fhi : 0u;
+    const int gn = g == 0 ? -1 : g + 1 < ng ? g + 1 : 0;
+    if (gn >= 0) fetch(gn);
+    const int h0 = gr[g].start, h1 = h0 + gr[g].n0 + gr[g].n1 + gr[g].n2;
+    if constexpr (R == Q) {
+      WHop<T> h = load_hop<T>(hp + h0);
+      for (int i = h0; i < h1;) {
+        const V* src = tl + (lane ^ h.la);
 #pragma unroll
-      for (int q = 0; q < R; ++q) nx[q] = ldg(ub, row[q] ^ f);
-    }
-    const int h0 = gr[cur].start, e0 = h0 + gr[cur].n0, e1 = e0 + gr[cur].n1, e2 = e1 + gr[cur].n2;
-    int h = h0;
-    for (; h < e0; ++h) {        // m = 0
-      const uint32_t flo = hp[h].flo;
-      const T c = hp[h].cs;
+        for (int q = 0; q < Q; ++q) x[q] = src[q * kWideBlock];
+        wide_run<W, T>(acc, x, hp, i, h, wbase);
+      }
+    } else {
+      // one wave's hops are a chain of dependent reads: kWideAhead at a time
+      for (int i = h0; i < h1; i += kWideAhead) {
+        WHop<T> h[kWideAhead];
+        V xa[kWideAhead][R];
 #pragma unroll
-      for (int q = 0; q < R; ++q) acc[q] += c * tl[(lane + q * kWideBlock) ^ flo];
-    }
-    for (; h < e1; ++h) {        // coefficient uniform over the tile; zero ones skipped
-      const T c = (__builtin_popcount(t.base & hp[h].m) & 1u) ? hp[h].cd : hp[h].cs;
-      if (c == T(0)) continue;
-      const uint32_t flo = hp[h].flo;
+        for (int u = 0; u < kWideAhead; ++u) h[u] = load_hop<T>(hp + i + u);
 #pragma unroll
-      for (int q = 0; q < R; ++q) acc[q] += c * tl[(lane + q * kWideBlock) ^ flo];
-    }
-    for (; h < e2; ++h) {        // per-row coefficient
-      const uint32_t flo = hp[h].flo;
-      V a[R];
+        for (int u = 0; u < kWideAhead; ++u)
 #pragma unroll
-      for (int q = 0; q < R; ++q) a[q] = tl[(lane + q * kWideBlock) ^ flo];
-      T c[R];
-      row_coefs(hp[h].m, hp[h].cs, hp[h].cd, c);
+          for (int r = 0; r < R; ++r) xa[u][r] = tl[(lane ^ h[u].la) + ((q0 + r) ^ h[u].fq) * kWideBlock];
 #pragma unroll
-      for (int q = 0; q < R; ++q) acc[q] += c[q] * a[q];
+        for (int u = 0; u < kWideAhead; ++u)
+          if (i + u < h1) hop_part(h[u], xa[u]);
+      }
     }
     if (gn < 0) break;
     g = gn;
   }
 
+  // <u_j, r> over the tile, or over each of its kWideParts parts (wparts):
+  // per lane and part, then per wave, then over the waves in order
+  constexpr int RP = Q / kWideParts;           // register indexes of a part
+  const bool parts = sg.wparts != 1;
   double dq[W];
 #pragma unroll
   for (int e = 0; e < W; ++e) dq[e] = 0.0;
-  V up[R];
   if (uprev) {
 #pragma unroll
-    for (int q = 0; q < R; ++q) up[q] = ldg_nt(uprev, row[q]);
+    for (int r = 0; r < R; ++r) nx[r] = ldg_nt(uprev, row[r]);
   }
   const V sc = scur_of<T, 1>(st, cp, t.panel, 0, plain);
   V bp;
   if (uprev) bp = bps_of<T, 1>(st, cp, t.panel, 0);
 #pragma unroll
-  for (int q = 0; q < R; ++q) {
-    const V x = tl[lane + q * kWideBlock];   // the own row, staged last
-    V r = sc * (acc[q] + ldg_s(dg, row[q]) * x);
+  for (int r = 0; r < R; ++r) {
+    const V xo = tl[lane + (q0 + r) * kWideBlock];   // the own row, staged last
+    const T d = ldg_s(dg, row[r]);
+    V v;
+#pragma unroll
+    for (int e = 0; e < W; ++e) v[e] = sc[e] * fma_s(d, xo[e], acc[r * W + e]);
     if (uprev) {
 #pragma unroll
-      for (int e = 0; e < W; ++e) r[e] = fma_s(-bp[e], up[q][e], r[e]);
+      for (int e = 0; e < W; ++e) v[e] = fma_s(-bp[e], nx[r][e], v[e]);
     }
-    stg_stream<true>(out, row[q], r);
+    stg_stream<true>(out, row[r], v);
     if (dots) {
 #pragma unroll
-      for (int e = 0; e < W; ++e) dq[e] += (double)x[e] * (double)r[e];
+      for (int e = 0; e < W; ++e) dq[e] += (double)xo[e] * (double)v[e];
+      if ((r + 1) % RP == 0 && (parts || r + 1 == R)) {
+#pragma unroll
+        for (int e = 0; e < W; ++e) dq[e] = wave_sum(dq[e]);
+        if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+          for (int e = 0; e < W; ++e) lds[((parts ? r / RP : 0) * NW + wave) * W + e] = dq[e];
+        }
+#pragma unroll
+        for (int e = 0; e < W; ++e) dq[e] = 0.0;
+      }
     }
   }
   if (!dots) return;
-  // fixed-order sum over the workgroup's NW waves
-#pragma unroll
-  for (int e = 0; e < W; ++e) dq[e] = wave_sum(dq[e]);
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-    for (int e = 0; e < W; ++e) lds[wave * W + e] = dq[e];
-  }
   __syncthreads();
-  if (threadIdx.x < W) {
+  const int np = parts ? R / RP : 1;           // partial sums of this workgroup
+  if ((int)threadIdx.x < np * W) {
+    const int pi = threadIdx.x / W, e = threadIdx.x % W;
     double tot = 0.0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) tot += lds[w * W + threadIdx.x];
-    sg.part[(uint64_t)t.tile * cp + t.panel * W + threadIdx.x] = tot;
+    for (int w = 0; w < NW; ++w) tot += lds[(pi * NW + w) * W + e];
+    sg.part[(uint64_t)(t.tile * sg.wparts + t.part + pi) * cp + t.panel * W + e] = tot;
   }
 }
 
@@ -2218,9 +2285,11 @@ hipError_t launch_apply(const Seg* segs, int nseg, int ntiles, int slab, hipStre
 }
 
 template <typename T>
-hipError_t launch_apply_wide(const Seg* segs, int nseg, int ntiles, hipStream_t st) {
-  if (ntiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL((k_apply_wide<T>), dim3(ntiles), dim3(kWideBlock), 0, st, segs, nseg);
+hipError_t launch_apply_wide(const Seg* segs, int nseg, int ntiles, int nsplit, hipStream_t st) {
+  if (ntiles > 0)
+    hipLaunchKernelGGL((k_apply_wide<T, kWideRows>), dim3(ntiles), dim3(kWideBlock), 0, st, segs, nseg);
+  if (nsplit > 0)
+    hipLaunchKernelGGL((k_apply_wide<T, kWideRows / kWideParts>), dim3(nsplit), dim3(kWideBlock), 0, st, segs, nseg);
   return hipGetLastError();
 }
 
@@ -2397,8 +2466,8 @@ template hipError_t launch_norm<float>(const Seg*, int, int, int, hipStream_t);
 template hipError_t launch_norm<double>(const Seg*, int, int, int, hipStream_t);
 template hipError_t launch_apply<float>(const Seg*, int, int, int, hipStream_t);
 template hipError_t launch_apply<double>(const Seg*, int, int, int, hipStream_t);
-template hipError_t launch_apply_wide<float>(const Seg*, int, int, hipStream_t);
-template hipError_t launch_apply_wide<double>(const Seg*, int, int, hipStream_t);
+template hipError_t launch_apply_wide<float>(const Seg*, int, int, int, hipStream_t);
+template hipError_t launch_apply_wide<double>(const Seg*, int, int, int, hipStream_t);
 template hipError_t launch_xz_pass<float>(int, const Seg*, int, int, hipStream_t, int);
 template hipError_t launch_xz_split<float>(int, const Seg*, int, int, hipStream_t);
 template hipError_t launch_xz_split<double>(int, const Seg*, int, int, hipStream_t);

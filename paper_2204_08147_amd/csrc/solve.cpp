@@ -223,12 +223,12 @@ Seg make_seg(const SegPlan& g, const OpDevice* op, char* base, int mode, int sta
   Seg s{};
   s.nbits = g.nbits;
   s.n_row_tiles = g.n_row_tiles;
+  s.P = g.P;
   bind_apply(s, op);
   // FP64 transform steps assemble <u_j, r_j> from XP_COUNT planes of x_tiles
   // rows each (n_row_tiles = dim / 256 rows leave room for them)
   static_assert(XP_COUNT * kBlock <= (1 << kXzTileBits), "partial-sum planes exceed the part buffer");
   s.xdots = op->xz && g.prec == RDM_FP64 ? 1 : 0;
-  s.P = g.P;
   s.S = g.S;
   s.rpl = g.rpl;
   s.C = g.C;
@@ -367,11 +367,16 @@ void bind_apply(Seg& s, const OpDevice* op) {
   s.nm_rows = s.ap_rows;
   s.wide = 0;
   s.wbits = 0;
+  s.wwin = 0;
+  s.wtab = nullptr;
+  s.wparts = 1;
   if (op->wide && !op->xz && s.nbits >= kWideBits) {
     // the apply on bit-set tiles: their tables, one partial-sum row per tile
     // (the norm step keeps its 256-row tiles)
     s.wide = 1;
     s.wbits = op->wbits;
+    s.wwin = op->wwin;
+    s.wtab = op->wtab;
     s.hops = op->whops;
     s.groups = op->wgroups;
     s.thin = op->wthin;
@@ -379,7 +384,11 @@ void bind_apply(Seg& s, const OpDevice* op) {
     s.nt0 = op->wnt[0];
     s.nt1 = op->wnt[1];
     s.nt2 = op->wnt[2];
-    s.ap_rows = 1 << (s.nbits - kWideBits);
+    // few tiles: a launch of such segments only may take kWideParts workgroups
+    // per tile (assign_tiles), so the tiles have as many partial sums in every
+    // launch
+    s.wparts = (s.P << (s.nbits - kWideBits)) < kWideSplit ? kWideParts : 1;
+    s.ap_rows = s.wparts << (s.nbits - kWideBits);
   }
 }
 
@@ -390,13 +399,18 @@ Launch assign_tiles(std::vector<Seg>& segs) {
   // outside a launch get no workgroups in it (their base is the running
   // count, which the kernels' binary search never resolves to them).
   Launch L;
+  int wtiles = 0;
+  for (const auto& sg : segs)
+    if (sg.wide) wtiles += sg.P << (sg.nbits - kWideBits);
+  const bool split = wtiles < kWideSplit;
   for (auto& sg : segs) {
     sg.tile_base = L.norm;
     if (!sg.xz) L.norm += sg.n_row_tiles * (sg.P / sg.S);
     sg.ap_base = L.apply;
     if (!sg.xz && !sg.wide) L.apply += sg.n_row_tiles * (sg.P / sg.S);
     sg.wp_base = L.wide;
-    if (sg.wide) L.wide += (1 << (sg.nbits - kWideBits)) * sg.P;
+    sg.ws_base = L.wsplit;
+    if (sg.wide) (split ? L.wsplit : L.wide) += ((split ? kWideParts : 1) << (sg.nbits - kWideBits)) * sg.P;
     sg.x_base = L.xz;
     if (sg.xz) {
       L.xz += sg.x_tiles * sg.P;
@@ -454,7 +468,8 @@ rdm_status launch_step(int prec, const Seg* dsegs, int nseg, const Launch& L, in
   if (tm) RDM_HIP(tm->apply.mark(st));
   RDM_HIP(d ? launch_apply<double>(dsegs, nseg, L.apply, slab, st)
             : launch_apply<float>(dsegs, nseg, L.apply, slab, st));
-  RDM_HIP(d ? launch_apply_wide<double>(dsegs, nseg, L.wide, st) : launch_apply_wide<float>(dsegs, nseg, L.wide, st));
+  RDM_HIP(d ? launch_apply_wide<double>(dsegs, nseg, L.wide, L.wsplit, st)
+            : launch_apply_wide<float>(dsegs, nseg, L.wide, L.wsplit, st));
   RDM_HIP(d ? launch_xz_lanczos<double>(2, false, dsegs, nseg, L.xz, 0, st)
             : launch_xz_lanczos<float>(2, false, dsegs, nseg, L.xz, 0, st));
   if (tm) RDM_HIP(tm->apply.mark(st));
@@ -641,13 +656,13 @@ namespace {
 struct GraphKey {
   int device;
   const void* dsegs;
-  int nseg, norm, apply, wide, xz, slab, cmax, prec, nsteps;
+  int nseg, norm, apply, wide, wsplit, xz, slab, cmax, prec, nsteps;
   int variants;  // bit (3 * regen + geometry) set when that strided variant runs, bit
                  // (6 + geometry) when that YY strided variant runs
   bool operator<(const GraphKey& o) const {
-    return std::tie(device, dsegs, nseg, norm, apply, wide, xz, slab, cmax, prec, nsteps, variants) <
-           std::tie(o.device, o.dsegs, o.nseg, o.norm, o.apply, o.wide, o.xz, o.slab, o.cmax, o.prec, o.nsteps,
-                    o.variants);
+    return std::tie(device, dsegs, nseg, norm, apply, wide, wsplit, xz, slab, cmax, prec, nsteps, variants) <
+           std::tie(o.device, o.dsegs, o.nseg, o.norm, o.apply, o.wide, o.wsplit, o.xz, o.slab, o.cmax, o.prec,
+                    o.nsteps, o.variants);
   }
 };
 int launch_variants(const Launch& L) {
@@ -713,7 +728,8 @@ rdm_status graph_steps_locked(int prec, Seg* dsegs, int nseg, const Launch& L, i
   } else {
     gs = its->second;
   }
-  const GraphKey key{dev, dsegs, nseg, L.norm, L.apply, L.wide, L.xz, slab, cmax, prec, nsteps, launch_variants(L)};
+  const GraphKey key{dev, dsegs, nseg, L.norm, L.apply, L.wide, L.wsplit, L.xz, slab, cmax, prec, nsteps,
+                     launch_variants(L)};
   hipGraphExec_t exec = nullptr;
   auto it = g_graphs.find(key);
   if (it != g_graphs.end()) {

@@ -117,13 +117,13 @@ rdm_status bind_ops(InstRun& r, hipStream_t st, bool build_tables = true);
 Seg seg_of(const InstRun& r, int which, int mode, double tau);
 int common_slab(std::vector<Seg>& segs);
 // Operator tables of a segment's apply (hop tables or transform).  Needs
-// nbits and n_row_tiles set.
+// nbits, P and n_row_tiles set.
 // A wide operator's segment takes the bit-set tables (Seg::wide).
 void bind_apply(Seg& s, const OpDevice* op);
 // workgroups of the norm launch and of the three kinds of apply launch
 struct Launch {
   int norm = 0, apply = 0, xz = 0;
-  int wide = 0;  // workgroups of the apply on bit-set tiles
+  int wide = 0, wsplit = 0;  // workgroups of the apply on bit-set tiles: a whole tile each, or kWideParts per tile
   // transform segments in each mode, by strided geometry (XG_SHALLOW,
   // XG_DEEP, XG_SPLIT); xy: those with a YY part
   bool xz_lanczos[3] = {false, false, false}, xz_regen[3] = {false, false, false};
