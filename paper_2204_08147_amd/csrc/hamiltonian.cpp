@@ -36,25 +36,28 @@ uint32_t expand_bits(uint32_t x, uint32_t mask) {
   return r;
 }
 
-// distinct nonzero partner-tile offsets f & ~B over the flip masks
-int distinct_partners(const std::vector<uint32_t>& flips, uint32_t B) {
-  std::vector<uint32_t> o;
-  for (uint32_t f : flips)
-    if (f & ~B) o.push_back(f & ~B);
-  std::sort(o.begin(), o.end());
-  return (int)(std::unique(o.begin(), o.end()) - o.begin());
+// the distinct nonzero values of x & ~B, sorted
+void reduce_flips(std::vector<uint32_t>& x, uint32_t B) {
+  for (uint32_t& f : x) f &= ~B;
+  std::sort(x.begin(), x.end());
+  x.erase(std::unique(x.begin(), x.end()), x.end());
+  if (!x.empty() && x[0] == 0u) x.erase(x.begin());
 }
 
 // Tile bits B of the bit-set tiles: the kWideLowBits lowest row bits (256-byte
 // runs per 16 lanes), then one bit at a time the one that leaves the fewest
-// distinct partner tiles (the lowest such bit on ties), kWideBits in all.
-uint32_t choose_tile_bits(const std::vector<uint32_t>& flips, int nbits) {
+// distinct partner tiles f & ~B (the lowest such bit on ties), kWideBits in all.
+uint32_t choose_tile_bits(std::vector<uint32_t> flips, int nbits) {
   uint32_t B = (1u << kWideLowBits) - 1u;
+  reduce_flips(flips, B);
   while (__builtin_popcount(B) < kWideBits) {
     int best = -1, best_n = 0;
     for (int b = kWideLowBits; b < nbits; ++b) {
       if ((B >> b) & 1u) continue;
-      const int n = distinct_partners(flips, B | (1u << b));
+      // without bit b the flips that hold it vanish or fall on another one
+      int n = (int)flips.size();
+      for (uint32_t f : flips)
+        if (((f >> b) & 1u) && (f == 1u << b || std::binary_search(flips.begin(), flips.end(), f ^ (1u << b)))) --n;
       if (best < 0 || n < best_n) {
         best = b;
         best_n = n;
@@ -62,6 +65,7 @@ uint32_t choose_tile_bits(const std::vector<uint32_t>& flips, int nbits) {
     }
     if (best < 0) break;  // fewer than kWideBits bits: callers need nbits >= kWideBits
     B |= 1u << best;
+    reduce_flips(flips, B);
   }
   return B;
 }
@@ -283,12 +287,14 @@ void compile(const rdm_hamiltonian& h, int first_site, OpTables& t) {
         t.wt_cd.push_back(x.cd);
       }
     }
-    std::vector<uint32_t> order;
-    for (uint32_t f : t.wt_f) order.push_back(f & ~B);
-    for (size_t g = 1; g < t.wgroups.size(); ++g) order.push_back(t.wgroups[g].fhi);
-    t.wwin = choose_window_bits(order, B, t.nbits);
     const int wpartners = (int)(t.wgroups.size() - 1 + t.wt_f.size());
     t.wide = !use && h.apply != RDM_APPLY_HOPS_ROWS && wpartners < partners;
+    if (t.wide) {
+      std::vector<uint32_t> order;
+      for (uint32_t f : t.wt_f) order.push_back(f & ~B);
+      for (size_t g = 1; g < t.wgroups.size(); ++g) order.push_back(t.wgroups[g].fhi);
+      t.wwin = choose_window_bits(order, B, t.nbits);
+    }
   }
   if (use) {
     t.xterms = xt;

@@ -312,6 +312,36 @@ template <typename T>
 hipError_t launch_start_block(int ns_log, int nb, int C, uint64_t seed, int kind, T* out,
                               int nbits, int cpad, hipStream_t st);
 
+// Function-approximation weights from the recurrence coefficients on the
+// device (tridiag.hip): k <= kTriMaxK steps and at most kTriMaxTerms terms.
+constexpr int kTriRows = 4;                  // rows of T per lane at most
+constexpr int kTriMaxK = 64 * kTriRows;
+constexpr int kTriBetas = 16;                // temperatures per launch
+constexpr int kTriMaxTerms = 4000;
+// Lanczos coefficients of one segment ([k][cpad]) and its Krylov sizes
+struct TriSeg {
+  const double *ha, *hb, *hs;
+  const int32_t* kc;
+  int32_t k, cpad, C;
+};
+// scratch (doubles): smallest eigenvalue and upper bound per column of H_t,
+// the same of H_b, the quadratures [n_beta][b.C] (over |v|^2 = 1 / s_1^2),
+// then kTriOut values {E0, E0b, broken-down columns of H_t, of H_b}
+// (NaN for E0 / E0b when a coefficient is not finite)
+constexpr int kTriOut = 4;
+struct TriArgs {
+  TriSeg t, b;
+  double* scratch;
+  void* yt;                                  // [n_beta][t.k][t.cpad] in T
+  double bscale;                             // factor of the weights
+  int32_t n_beta, beta0, max_terms;
+  double beta[kTriBetas];
+  // terms of exp(-z (t + 1)) for z >= 1: e^-z I_n(z) < e^(-n^2 / 2z) < e^-50
+  __host__ __device__ static int n_terms(double z) { return 30 + (int)(10.0 * sqrt(z)); }
+};
+template <typename T>
+hipError_t launch_tri(const TriArgs& args, const double* betas, int n_beta, double zmax, hipStream_t st);
+
 // Bath-site sign correlations of the random bath vectors: for bath vectors
 // j < nv and bath bits p < nb, the integer sum over b of s_b s_(b xor 2^p)
 // (s_b = +-1 the signs of v_j), as per-block partials

@@ -204,7 +204,7 @@ void rdm_server::finish_loop() {
     bool requeued = false;
     if (q == RDM_OK && cancelled(r)) q = RDM_E_CANCELLED;
     if (q == RDM_OK && r->phase == 0) {
-      q = host_phase(r->run, fs);
+      q = weights_phase(r->run, fs);
       if (q == RDM_OK && r->plan.two_pass) {
         r->phase = 1;
         r->steps = 0;

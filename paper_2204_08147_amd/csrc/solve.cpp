@@ -558,8 +558,86 @@ rdm_status host_phase_t(InstRun& r, hipStream_t st) {
 
 }  // namespace
 
-rdm_status host_phase(InstRun& r, hipStream_t st) {
-  return r.plan->prec == RDM_FP64 ? host_phase_t<double>(r, st) : host_phase_t<float>(r, st);
+namespace {
+
+// Scratch of the device weights: the Gram's partial sums and sums, which
+// nothing reads before the Gram.  They hold n_beta n_v d_s^2 doubles at least
+// each, in 256-byte units, behind each other: 2 (d_s + 1) n_v + n_beta n_v +
+// kTriOut fit for every d_s >= 2.
+double* tri_scratch(const InstRun& r) { return (double*)(r.base + r.plan->o_gpart); }
+size_t tri_doubles(const InstPlan& p) {
+  return 2 * (size_t)(p.tot.C + p.bath.C) + (size_t)p.n_beta * p.bath.C + kTriOut;
+}
+
+// an upper bound of |H| (sum of the coefficients' magnitudes)
+double norm_bound(const OpTables& t) {
+  double s = 0.0;
+  for (const auto& d : t.diag) s += std::fabs(d.c);
+  for (double c : t.uc) s += std::fabs(c);
+  for (size_t i = 0; i < t.pcs.size(); ++i) s += std::max(std::fabs(t.pcs[i]), std::fabs(t.pcd[i]));
+  return s;
+}
+
+}  // namespace
+
+rdm_status weights_launch(InstRun& r, hipStream_t st) {
+  const InstPlan& p = *r.plan;
+  // half the width of T's Gershgorin interval is at most 2 |H|, so z =
+  // (beta / 2) * that is at most beta |H| (FP32 recurrences: to rounding)
+  double bmax = 0.0;
+  for (double b : r.betas) bmax = std::max(bmax, b);
+  const double zmax = std::max(1.0, 1.01 * bmax * std::max(norm_bound(p.h->op[0]), norm_bound(p.h->op[1])));
+  r.on_device = std::max(p.k, p.kb) <= kTriMaxK && zmax < 1e8 && TriArgs::n_terms(zmax) <= kTriMaxTerms &&
+                tri_doubles(p) * 8 <= p.o_gseg - p.o_gpart;
+  if (!r.on_device) return RDM_OK;
+  TriArgs a{};
+  for (int w = 0; w < 2; ++w) {
+    const SegPlan& g = w == 0 ? p.tot : p.bath;
+    TriSeg& s = w == 0 ? a.t : a.b;
+    s.ha = (const double*)(r.base + g.o_ha);
+    s.hb = (const double*)(r.base + g.o_hb);
+    s.hs = (const double*)(r.base + g.o_hs);
+    s.kc = (const int32_t*)(r.base + g.o_kc);
+    s.k = g.k;
+    s.cpad = g.cpad;
+    s.C = g.C;
+  }
+  a.scratch = tri_scratch(r);
+  a.yt = r.base + p.o_y;
+  a.bscale = r.op_t->xz ? kXzBasisScale : 1.0;
+  a.n_beta = p.n_beta;
+  RDM_HIP(p.prec == RDM_FP64 ? launch_tri<double>(a, r.betas.data(), p.n_beta, zmax, st)
+                             : launch_tri<float>(a, r.betas.data(), p.n_beta, zmax, st));
+  return RDM_OK;
+}
+
+rdm_status weights_collect(InstRun& r, hipStream_t st) {
+  const InstPlan& p = *r.plan;
+  if (!r.on_device) return p.prec == RDM_FP64 ? host_phase_t<double>(r, st) : host_phase_t<float>(r, st);
+  std::vector<double> v(tri_doubles(p));
+  RDM_HIP(hipMemcpyAsync(v.data(), tri_scratch(r), v.size() * 8, hipMemcpyDeviceToHost, st));
+  RDM_HIP(hipStreamSynchronize(st));
+  const double* quad = v.data() + 2 * (p.tot.C + p.bath.C);
+  const double* out = quad + (size_t)p.n_beta * p.bath.C;
+  if (!std::isfinite(out[0]) || !std::isfinite(out[1])) {
+    set_error("non-finite Lanczos coefficients");
+    return RDM_E_NONFINITE;
+  }
+  r.e0 = out[0];
+  r.e0b = out[1];
+  r.n_break_t = (int)out[2];
+  r.n_break_b = (int)out[3];
+  r.mb.assign(p.n_beta, 0.0);
+  for (int b = 0; b < p.n_beta; ++b) {
+    for (int c = 0; c < p.bath.C; ++c) r.mb[b] += quad[(size_t)b * p.bath.C + c];
+    r.mb[b] /= p.n_v;
+  }
+  return RDM_OK;
+}
+
+rdm_status weights_phase(InstRun& r, hipStream_t st) {
+  const rdm_status s = weights_launch(r, st);
+  return s != RDM_OK ? s : weights_collect(r, st);
 }
 
 rdm_status gram_phase(InstRun& r, hipStream_t st, Timers* tg) {
@@ -905,7 +983,9 @@ rdm_status execute(std::vector<InstRun>& runs, char* ws, hipStream_t st, double 
   if (s != RDM_OK) return s;
   {
     Range hr("rdm host phase");
-    for (auto& r : runs) r.status = host_phase(r, st);
+    for (auto& r : runs) r.status = weights_launch(r, st);
+    for (auto& r : runs)
+      if (r.status == RDM_OK) r.status = weights_collect(r, st);
   }
   // pass 2 (two-pass plans): regenerate u_j from the stored coefficients
   segs.clear();

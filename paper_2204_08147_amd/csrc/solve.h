@@ -95,6 +95,7 @@ struct InstRun {
   double e0 = 0, e0b = 0;
   int n_break_t = 0, n_break_b = 0;
   std::vector<double> mb, gsum;
+  bool on_device = false;  // the weights are the device's (weights_launch)
   double t_apply_ms = 0, t_norm_ms = 0, t_gram_ms = 0, t_xz1_ms = 0;
   double t_replay_ms = 0;  // mean replayed step (ms) and steps replayed (profile = 2)
   int replay_steps = 0;
@@ -148,7 +149,13 @@ rdm_status run_phase(std::vector<Seg>& hsegs, Seg* dsegs, int prec, int phase, h
 // Panels per lane for a launch over these segments: the cached measurement
 // for the shape of the largest one, else one panel.
 int tuned_slab(int prec, std::vector<Seg>& segs);
-rdm_status host_phase(InstRun& r, hipStream_t st);   // synchronous
+// T_k exponentials: E0, the recombination weights and the bath quadrature.
+// weights_launch enqueues the device kernels when the instance is in their
+// range (then r.on_device); weights_collect waits for them, or does the whole
+// phase on the host.  weights_phase: both.
+rdm_status weights_launch(InstRun& r, hipStream_t st);
+rdm_status weights_collect(InstRun& r, hipStream_t st);
+rdm_status weights_phase(InstRun& r, hipStream_t st);
 rdm_status gram_phase(InstRun& r, hipStream_t st, Timers* tg);  // synchronous
 rdm_status finalize(const InstRun& r, rdm_result* out);
 

@@ -1,0 +1,38 @@
+"""GPU solves at the edges of the device's function-approximation weights
+(one, two and four rows of T per lane, and the host routine beyond; exponents
+from nearly zero to large) against the oracle's eigenvector form."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+rdm = pytest.importorskip("paper_2204_08147_amd")
+
+from oracle import lanczos as olz  # noqa: E402
+from workloads import random_dense_terms  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("k", [1, 2, 63, 64, 65, 128, 129, 256, 257])
+def test_weights_match_oracle(k):
+    inst = random_dense_terms(1, 8, 900 + k, k=k, betas=(1e-9, 1e-3, 0.7, 30.0), n_v=2)
+    got = rdm.solve(rdm.Hamiltonian.from_instance(inst), inst.betas, inst.n_v, inst.k, inst.seed, precision="fp64")
+    want = olz.solve(inst)["results"]
+    for b, w in enumerate(want):
+        # the FP64 parity bar; H* = -ln(..)/beta + .. loses 1 / beta of it
+        assert np.linalg.norm(got["rho"][b] - w["rho"]) < 1e-10 * np.linalg.norm(w["rho"])
+        tol = 1e-10 * max(1.0, 1e-5 / inst.betas[b])
+        assert np.linalg.norm(got["h_star"][b] - w["h_star"]) < 10 * tol * max(1.0, np.linalg.norm(w["h_star"]))
+        assert abs(got["log_z"][b] - w["log_z"]) < 1e-10 * max(1.0, abs(w["log_z"]))
+        assert abs(got["entropy"][b] - w["entropy"]) < 1e-10
+
+
+def test_many_temperatures_in_one_solve():
+    # more than one launch's worth of temperatures, each as if solved alone
+    inst = random_dense_terms(2, 7, 950, k=30, betas=tuple(0.05 * (b + 1) for b in range(37)), n_v=3)
+    h = rdm.Hamiltonian.from_instance(inst)
+    got = rdm.solve(h, inst.betas, inst.n_v, inst.k, inst.seed, precision="mixed")
+    for b in (0, 15, 16, 31, 32, 36):
+        one = rdm.solve(h, inst.betas[b:b + 1], inst.n_v, inst.k, inst.seed, precision="mixed")
+        assert np.linalg.norm(got["rho"][b] - one["rho"][0]) < 1e-5 * np.linalg.norm(one["rho"][0])
+        assert abs(got["log_z"][b] - one["log_z"][0]) < 1e-5
