@@ -49,9 +49,12 @@ rdm_status block_plan(BlockPlan& bp, const rdm_hamiltonian* h, int n_beta, int n
   bp.G = bp.cpad / bp.ds;
   bp.n_cb = bp.cpad / bp.CB;
   bp.blk = bp.dim * bp.cpad;
-  // rows per lane so that at most ~1024 row tiles feed each reduction
+  // rows per lane so that at most ~1024 row tiles feed each reduction and the
+  // updates run kUpdateGroups workgroups (each ends in a reduction of its
+  // d_s x d_s sums that costs as much as a row per lane)
+  constexpr uint64_t kUpdateGroups = 4096;
   const uint64_t rows_per_tile = std::max<uint64_t>(kBlock, (bp.dim + 1023) / 1024);
-  bp.rpl = (int)((rows_per_tile + kBlock - 1) / kBlock);
+  bp.rpl = (int)std::max((rows_per_tile + kBlock - 1) / kBlock, bp.dim * bp.n_cb / (kBlock * kUpdateGroups));
   bp.n_rt = (int)((bp.dim + (uint64_t)kBlock * bp.rpl - 1) / ((uint64_t)kBlock * bp.rpl));
   const int NE = bp.ds * bp.ds;
   // header: three apply segments (one per ring slot), the bath segment, BSeg

@@ -168,6 +168,47 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double* lds, double* 
   }
 }
 
+// The same for NV = a power of two up to 64 values, folding the values as the
+// lanes combine: at each of the first log2 NV exchanges a lane hands over the
+// half of its values that its partner goes on with, so a wave takes NV - 1 +
+// (6 - log2 NV) exchanges instead of 6 NV.  Threads 0..NV-1 receive the totals.
+template <int NV, int O = 1, int N = NV>
+__device__ __forceinline__ void wave_fold(double (&v)[NV], int lane) {
+  if constexpr (O < 64) {
+    if constexpr (N > 1) {
+      constexpr int H = N / 2;
+      const bool up = (lane & O) != 0;     // these lanes keep the upper half
+#pragma unroll
+      for (int i = 0; i < H; ++i) {
+        const double keep = up ? v[i + H] : v[i], give = up ? v[i] : v[i + H];
+        v[i] = keep + __shfl_xor(give, O, 64);
+      }
+      wave_fold<NV, 2 * O, H>(v, lane);
+    } else {
+      v[0] += __shfl_xor(v[0], O, 64);
+      wave_fold<NV, 2 * O, 1>(v, lane);
+    }
+  }
+}
+template <int NV>
+__device__ __forceinline__ void block_sum_fold(double (&v)[NV], double* lds, double* tot) {
+  static_assert(NV <= 64 && (NV & (NV - 1)) == 0, "a power of two of at most one value per lane");
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  wave_fold(v, lane);
+  // lane bits 0 .. log2 NV - 1 hold the value's index, its highest bit first
+  if (lane < NV) {
+    int idx = 0;
+#pragma unroll
+    for (int b = 1, h = NV >> 1; h > 0; b <<= 1, h >>= 1) idx |= (lane & b) ? h : 0;
+    lds[wave * NV + idx] = v[0];
+  }
+  __syncthreads();
+  if (threadIdx.x < NV) {
+    const int t = threadIdx.x;
+    *tot = ((lds[t] + lds[NV + t]) + lds[2 * NV + t]) + lds[3 * NV + t];
+  }
+}
+
 // Sum the lane values v over the workgroup and store them at plane `plane`
 // (XP_*), row tile rt, columns panel0 * W .. + W - 1, times scale.
 template <int W>
@@ -1676,8 +1717,14 @@ __device__ __forceinline__ typename PanelT<T>::V* blk_slot(const CONST_AS BSeg& 
   return (typename PanelT<T>::V*)bs.Q + (uint64_t)((j - 1) % 3) * (bs.blk / PanelT<T>::W);
 }
 
-template <typename T, int DS>
-__global__ __launch_bounds__(kBlock) void k_block_update(const BSeg* __restrict__ bsp, int phase, int j) {
+// The d_s x d_s matrices of a phase are read into registers before the rows
+// (d_s <= 4).  Bound by its streams (4, 3, 2 and 2 blocks in the four phases):
+// 28 FP32 columns on 19 sites took 54 us per launch with a shuffle tree per
+// entry on every second row and the matrices re-read and converted per row;
+// now 26 (36, 28, 20 and 19 us: 6.6, 6.3, 5.9 and 6.2 TB/s).
+template <typename T, int DS, int PHASE>
+__global__ __launch_bounds__(kBlock) void k_block_update(const BSeg* __restrict__ bsp, int j) {
+  constexpr int phase = PHASE;
   using V = typename PanelT<T>::V;
   constexpr int W = PanelT<T>::W;
   constexpr int CB = DS > W ? DS : W;
@@ -1693,8 +1740,16 @@ __global__ __launch_bounds__(kBlock) void k_block_update(const BSeg* __restrict_
   const int g0 = cb * NG;
   const int G = bs.G;
   const CONST_AS double* mats = (const CONST_AS double*)bs.mats;
-  auto mat = [&](int which, int i, int a, int b) -> T {
-    return (T)mats[((uint64_t)which * G + g0 + i) * NE + a * DS + b];
+  constexpr int BM = PHASE == BLK_A ? BM_BPREV : PHASE == BLK_G ? BM_A : BM_RINV;
+  constexpr bool KEEP = DS <= 4;
+  T m[KEEP ? NG * NE : 1];
+  if constexpr (KEEP) {
+#pragma unroll
+    for (int i = 0; i < NG * NE; ++i) m[i] = (T)mats[((uint64_t)BM * G + g0) * NE + i];
+  }
+  auto mat = [&](int i, int a, int b) -> T {
+    if constexpr (KEEP) return m[i * NE + a * DS + b];
+    else return (T)mats[((uint64_t)BM * G + g0 + i) * NE + a * DS + b];
   };
   V* qj = blk_slot<T>(bs, j) + (uint64_t)p0 * ps;
   V* qn = blk_slot<T>(bs, j + 1) + (uint64_t)p0 * ps;
@@ -1739,7 +1794,7 @@ __global__ __launch_bounds__(kBlock) void k_block_update(const BSeg* __restrict_
 #pragma unroll
           for (int a = 0; a < DS; ++a)
 #pragma unroll
-            for (int b = 0; b < DS; ++b) out[i * DS + a] = fma_s(-w[i * DS + b], mat(BM_BPREV, i, a, b), out[i * DS + a]);
+            for (int b = 0; b < DS; ++b) out[i * DS + a] = fma_s(-w[i * DS + b], mat(i, a, b), out[i * DS + a]);
       }
       store(rb, out);
 #pragma unroll
@@ -1759,7 +1814,7 @@ __global__ __launch_bounds__(kBlock) void k_block_update(const BSeg* __restrict_
         for (int a = 0; a < DS; ++a) {
           T z = x[i * DS + a];
 #pragma unroll
-          for (int b = 0; b < DS; ++b) z = fma_s(-y[i * DS + b], mat(BM_A, i, b, a), z);
+          for (int b = 0; b < DS; ++b) z = fma_s(-y[i * DS + b], mat(i, b, a), z);
           out[i * DS + a] = z;
         }
       store(rb, out);
@@ -1780,7 +1835,7 @@ __global__ __launch_bounds__(kBlock) void k_block_update(const BSeg* __restrict_
         for (int a = 0; a < DS; ++a) {
           T z = T(0);
 #pragma unroll
-          for (int b = 0; b <= a; ++b) z = fma_s(x[i * DS + b], mat(BM_RINV, i, b, a), z);
+          for (int b = 0; b <= a; ++b) z = fma_s(x[i * DS + b], mat(i, b, a), z);
           out[i * DS + a] = z;
         }
       store(qn, out);
@@ -1797,7 +1852,7 @@ __global__ __launch_bounds__(kBlock) void k_block_update(const BSeg* __restrict_
   }
   if (phase > BLK_G2) return;
   double tot;
-  block_sum<NG * NE>(dq, lds, &tot);
+  block_sum_fold<NG * NE>(dq, lds, &tot);
   if (threadIdx.x < NG * NE) bs.part[((uint64_t)rt * G + g0) * NE + threadIdx.x] = tot;
 }
 
@@ -1806,30 +1861,41 @@ __global__ __launch_bounds__(kBlock) void k_block_update(const BSeg* __restrict_
 template <int DS>
 __device__ double small_chol(const double* g, double* r) {
   double mn = INFINITY;
+#pragma unroll
   for (int i = 0; i < DS * DS; ++i) r[i] = 0.0;
+  // unrolled, so that r stays in registers; a failed pivot is remembered
+  double fail = 1.0;
+#pragma unroll
   for (int i = 0; i < DS; ++i) {
     double d = g[i * DS + i];
+#pragma unroll
     for (int k = 0; k < i; ++k) d -= r[k * DS + i] * r[k * DS + i];
-    if (!(d > 0.0)) return d > 0.0 ? mn : (d == d ? 0.0 : d);
+    if (!(d > 0.0) && fail > 0.0) fail = d == d ? 0.0 : d;
     const double rii = sqrt(d);
     r[i * DS + i] = rii;
     mn = fmin(mn, rii);
+#pragma unroll
     for (int jj = i + 1; jj < DS; ++jj) {
       double v = g[i * DS + jj];
+#pragma unroll
       for (int k = 0; k < i; ++k) v -= r[k * DS + i] * r[k * DS + jj];
       r[i * DS + jj] = v / rii;
     }
   }
-  return mn;
+  return fail > 0.0 ? mn : fail;
 }
 // inverse of an upper-triangular R with positive diagonal
 template <int DS>
 __device__ void small_triinv(const double* r, double* ri) {
+#pragma unroll
   for (int i = 0; i < DS * DS; ++i) ri[i] = 0.0;
+#pragma unroll
   for (int c = 0; c < DS; ++c) {
     ri[c * DS + c] = 1.0 / r[c * DS + c];
+#pragma unroll
     for (int i = c - 1; i >= 0; --i) {
       double v = 0.0;
+#pragma unroll
       for (int k = i + 1; k <= c; ++k) v += r[i * DS + k] * ri[k * DS + c];
       ri[i * DS + c] = -v / r[i * DS + i];
     }
@@ -1837,24 +1903,41 @@ __device__ void small_triinv(const double* r, double* ri) {
 }
 
 // one workgroup per group: sum the row-tile partials (fixed order), then the
-// small-matrix step of the phase
+// small-matrix step of the phase.  Lane i takes entry i mod NE of every
+// (kBlock / NE)-th row tile, so the NE entries of a tile are one contiguous
+// read and all entries are summed at once (one entry after the other, each
+// with its own tree, took 26 us per launch at d_s = 4 and 1024 row tiles; now
+// 9 us at 683).
 template <int DS>
 __global__ __launch_bounds__(kBlock) void k_block_reduce(const BSeg* __restrict__ bsp, int phase, int j) {
   constexpr int NE = DS * DS;
+  constexpr int NR = kBlock / NE;
   const BSeg& bs = *bsp;
   const int g = blockIdx.x, G = bs.G;
   __shared__ double red[kBlock];
   __shared__ double tot[NE];
-  for (int e = 0; e < NE; ++e) {
+  {
+    const int e = threadIdx.x % NE, r0 = threadIdx.x / NE;
+    const double* src = bs.part + (uint64_t)g * NE + e;
+    const uint64_t step = (uint64_t)G * NE;
     double acc = 0.0;
-    for (int t = threadIdx.x; t < bs.n_rt; t += kBlock) acc += bs.part[((uint64_t)t * G + g) * NE + e];
+    int t = r0;
+    for (; t + 3 * NR < bs.n_rt; t += 4 * NR) {    // four tiles' reads in flight
+      const double a0 = src[t * step], a1 = src[(t + NR) * step], a2 = src[(t + 2 * NR) * step],
+                   a3 = src[(t + 3 * NR) * step];
+      acc += a0;
+      acc += a1;
+      acc += a2;
+      acc += a3;
+    }
+    for (; t < bs.n_rt; t += NR) acc += src[t * step];
     red[threadIdx.x] = acc;
     __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    for (int w = NR / 2; w > 0; w >>= 1) {
+      if (r0 < w) red[threadIdx.x] += red[threadIdx.x + w * NE];
       __syncthreads();
     }
-    if (threadIdx.x == 0) tot[e] = red[0];
+    if (r0 == 0) tot[e] = red[e];
     __syncthreads();
   }
   if (threadIdx.x != 0) return;
@@ -2365,13 +2448,20 @@ hipError_t launch_xz_lanczos(int pass, bool regen, const Seg* segs, int nseg, in
   return hipGetLastError();
 }
 
+template <typename T, int DS>
+static void launch_block_phase(const BSeg* bs, int phase, int j, int n_wg, hipStream_t st) {
+  const dim3 grid(n_wg), blk(kBlock);
+  if (phase == BLK_A) hipLaunchKernelGGL((k_block_update<T, DS, BLK_A>), grid, blk, 0, st, bs, j);
+  else if (phase == BLK_G) hipLaunchKernelGGL((k_block_update<T, DS, BLK_G>), grid, blk, 0, st, bs, j);
+  else if (phase == BLK_G2) hipLaunchKernelGGL((k_block_update<T, DS, BLK_G2>), grid, blk, 0, st, bs, j);
+  else hipLaunchKernelGGL((k_block_update<T, DS, BLK_G2 + 1>), grid, blk, 0, st, bs, j);
+}
 template <typename T>
 hipError_t launch_block_update(const BSeg* bs, int ds, int phase, int j, int n_rt, int n_cb, hipStream_t st) {
-  const dim3 grid(n_rt * n_cb), blk(kBlock);
   switch (ds) {
-    case 2: hipLaunchKernelGGL((k_block_update<T, 2>), grid, blk, 0, st, bs, phase, j); break;
-    case 4: hipLaunchKernelGGL((k_block_update<T, 4>), grid, blk, 0, st, bs, phase, j); break;
-    default: hipLaunchKernelGGL((k_block_update<T, 8>), grid, blk, 0, st, bs, phase, j); break;
+    case 2: launch_block_phase<T, 2>(bs, phase, j, n_rt * n_cb, st); break;
+    case 4: launch_block_phase<T, 4>(bs, phase, j, n_rt * n_cb, st); break;
+    default: launch_block_phase<T, 8>(bs, phase, j, n_rt * n_cb, st); break;
   }
   return hipGetLastError();
 }
