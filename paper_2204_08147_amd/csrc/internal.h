@@ -291,7 +291,8 @@ hipError_t launch_xz_lanczos(int pass, bool regen, const Seg* segs, int nseg, in
 constexpr double kXzBasisScale = 1.0 / (1 << (kXzTileBits / 2));
 // Lanczos-step passes of the YY part (xy segments): 3 = Y <- W_lo T W_lo u~ / L
 // (contiguous), 4 = Y <- W_hi D_Y W_hi Y (strided; deep variant as for pass 1),
-// 5 = R <- R + W_lo T W_lo Y / L (contiguous), before pass 2
+// 5 = R <- R + W_lo T W_lo Y / L (contiguous), before pass 2 (FP64); FP32: 6 =
+// pass 5 and pass 2 on one tile
 hipError_t launch_red_beta(const Seg* segs, int nseg, int cmax, hipStream_t st);
 hipError_t launch_red_alpha(const Seg* segs, int nseg, int cmax, hipStream_t st);
 hipError_t launch_init_state(const Seg* segs, int nseg, int cmax, int phase, hipStream_t st);

@@ -127,6 +127,27 @@ __device__ __forceinline__ void stg_sel(V* base, uint32_t row, V v) {
   else stg(base, row, v);
 }
 
+// A row as a workgroup-uniform part and the lane's: the uniform part goes into
+// the scalar base of the access, so the rows of a lane's registers share one
+// vector offset.
+struct XRow {
+  uint32_t u, l;
+};
+template <typename V>
+__device__ __forceinline__ V ldg(const V* base, XRow r) { return ldg(base + r.u, r.l); }
+template <typename V>
+__device__ __forceinline__ void stg(V* base, XRow r, V v) { stg(base + r.u, r.l, v); }
+template <typename V>
+__device__ __forceinline__ V ldg_nt(const V* base, XRow r) { return ldg_nt(base + r.u, r.l); }
+template <bool NT, typename V>
+__device__ __forceinline__ void stg_stream(V* base, XRow r, V v) { stg_stream<NT>(base + r.u, r.l, v); }
+template <typename T>
+__device__ __forceinline__ T ldg_s(const T* base, XRow r) { return ldg_s(base + r.u, r.l); }
+template <bool NT, typename V>
+__device__ __forceinline__ V ldg_sel(const V* base, XRow r) { return ldg_sel<NT>(base + r.u, r.l); }
+template <bool NT, typename V>
+__device__ __forceinline__ void stg_sel(V* base, XRow r, V v) { stg_sel<NT>(base + r.u, r.l, v); }
+
 // Segment descriptors are read-only during a kernel: read them through the
 // constant address space so uniform fields come in with scalar loads.
 typedef Seg CSeg;
@@ -1113,7 +1134,7 @@ __device__ __forceinline__ void xz_high_transform(V (&v)[kXzRegs], V* lds, const
     const int m2 = 0xF & ~((1 << (lrb - 4)) - 1);
     xz_bfly(v, m2);
 #pragma unroll
-    for (int q = 0; q < kXzRegs; ++q) v[q] = xz_scale_quad(ldg_s(dx, row_of(xz_tau(2, l, q))), v[q], qf, QUAD);
+    for (int q = 0; q < kXzRegs; ++q) v[q] = xz_scale_quad(ldg_s(dx, row_of(2, q)), v[q], qf, QUAD);
     xz_bfly(v, m2);
   } else {
     const int m1 = 0xF & ~((1 << lrb) - 1);
@@ -1150,6 +1171,48 @@ __device__ __forceinline__ void yy_twist(V (&v)[kXzRegs], uint32_t row0, T scale
   }
 }
 
+// Rows of a strided tile: element tau of the tile is row ((tau >> lrb) <<
+// gshift) | fixed | (tau mod 2^lrb).  (arr, q): register q in arrangement arr;
+// the bits of q and of the lane never overlap, so the row is a uniform part
+// plus the lane's.
+struct XzRows {
+  int lrb, gshift;
+  uint32_t lrm, fixed, lane0, lane2;
+  __device__ __forceinline__ uint32_t part(uint32_t tau) const { return ((tau >> lrb) << gshift) | (tau & lrm); }
+  __device__ __forceinline__ XRow operator()(int arr, int q) const {
+    return XRow{fixed + part(xz_tau(arr, 0u, q)), arr == 0 ? lane0 : lane2};
+  }
+  __device__ __forceinline__ void init(int lrb_, int gshift_, uint32_t fixed_) {
+    lrb = lrb_;
+    gshift = gshift_;
+    lrm = (1u << lrb) - 1u;
+    fixed = fixed_;
+    lane0 = part(xz_tau(0, threadIdx.x, 0));
+    lane2 = part(xz_tau(2, threadIdx.x, 0));
+  }
+};
+// shallow and deep operators: every high-bit value, runs of 2^lrb rows from
+// rt * 2^lrb on
+__device__ __forceinline__ XzRows strided_rows(int nbits, uint32_t rt) {
+  XzRows r;
+  const int lrb = 2 * kXzTileBits - nbits;
+  r.init(lrb, kXzTileBits, rt << lrb);
+  return r;
+}
+// split operators: a tile of group A (bits 12 .. 12+a-1) or B (bits 12+a ..
+// N-1); the tile index rt holds the other group's bits above the g low-rest
+// bits lrb..11 of the row
+__device__ __forceinline__ XzRows split_rows(int nbits, bool B, uint32_t rt) {
+  XzRows r;
+  const int a = xz_split_a(nbits);
+  const int g = B ? nbits - kXzTileBits - a : a;
+  const int lrb = kXzTileBits - g;
+  const uint32_t lowrest = rt & ((1u << g) - 1u), other = rt >> g;
+  r.init(lrb, B ? kXzTileBits + a : kXzTileBits,
+         (lowrest << lrb) | (other << (B ? kXzTileBits : kXzTileBits + a)));
+  return r;
+}
+
 // In-place strided pass buf = W_hi D W_hi buf on the strided tile t of a
 // segment (the row map and cache hints of the strided passes below); QUAD as
 // in xz_high_transform.
@@ -1157,22 +1220,16 @@ template <typename T, bool DEEP, bool QUAD = false>
 __device__ __forceinline__ void xz_strided_inplace(const CONST_AS CSeg& sg, const Tile& t, typename PanelT<T>::V* buf,
                                                    const T* dd, typename PanelT<T>::V* lds, double* qf = nullptr) {
   using V = typename PanelT<T>::V;
-  const uint32_t l = threadIdx.x;
-  const int hb = sg.nbits - kXzTileBits;
-  const int lrb = kXzTileBits - hb;
-  const uint32_t lrm = (1u << lrb) - 1u;
-  const uint32_t base = (uint32_t)t.rtile << lrb;
-  auto row_of = [&](uint32_t tau) -> uint32_t {
-    return ((tau >> lrb) << kXzTileBits) | (base + (tau & lrm));
-  };
+  const XzRows row_of = strided_rows(sg.nbits, (uint32_t)t.rtile);
+  const int lrb = row_of.lrb;
   V v[kXzRegs];
   auto run = [&](auto nt_tag) {
     constexpr bool NT = decltype(nt_tag)::value;
 #pragma unroll
-    for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_sel<NT>((const V*)buf, row_of(xz_tau(0, l, q)));
+    for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_sel<NT>((const V*)buf, row_of(0, q));
     xz_high_transform<DEEP, QUAD>(v, lds, dd, t.rtile, lrb, row_of, qf);
 #pragma unroll
-    for (int q = 0; q < kXzRegs; ++q) stg_sel<NT>(buf, row_of(xz_tau(0, l, q)), v[q]);
+    for (int q = 0; q < kXzRegs; ++q) stg_sel<NT>(buf, row_of(0, q), v[q]);
   };
   if (!DEEP || lrb >= 3) run(std::true_type{});
   else run(std::false_type{});
@@ -1187,40 +1244,18 @@ __device__ __forceinline__ void xz_strided_inplace(const CONST_AS CSeg& sg, cons
 template <bool WITH_D, bool QUAD = false, typename T, typename V, typename RowOf>
 __device__ __forceinline__ void xz_group_transform(V (&v)[kXzRegs], V* lds, const T* dd, int lrb, RowOf row_of,
                                                    double* qf = nullptr) {
-  const uint32_t l = threadIdx.x;
   const int m2 = 0xF & ~((1 << (lrb - 4)) - 1);
   xz_bfly(v, 0xF);
   xz_rearrange(v, lds, 0, 2);
   xz_bfly(v, m2);
   if (WITH_D) {
 #pragma unroll
-    for (int q = 0; q < kXzRegs; ++q) v[q] = xz_scale_quad(ldg_s(dd, row_of(xz_tau(2, l, q))), v[q], qf, QUAD);
+    for (int q = 0; q < kXzRegs; ++q) v[q] = xz_scale_quad(ldg_s(dd, row_of(2, q)), v[q], qf, QUAD);
     xz_bfly(v, m2);
   }
   xz_rearrange(v, lds, 2, 0);
   if (WITH_D) xz_bfly(v, 0xF);
 }
-
-// Row of tau in a split tile of group A (B = false: bits 12 .. 12+a-1) or B
-// (bits 12+a .. N-1) of a segment on nbits bits; the tile index rt holds the
-// other group's bits above the g low-rest bits lrb..11 of the row.
-struct SplitRows {
-  int lrb;
-  uint32_t lrm, fixed;
-  int gshift;
-  __device__ __forceinline__ SplitRows(int nbits, bool B, uint32_t rt) {
-    const int a = xz_split_a(nbits);
-    const int g = B ? nbits - kXzTileBits - a : a;
-    lrb = kXzTileBits - g;
-    lrm = (1u << lrb) - 1u;
-    const uint32_t lowrest = rt & ((1u << g) - 1u), other = rt >> g;
-    gshift = B ? kXzTileBits + a : kXzTileBits;
-    fixed = (lowrest << lrb) | (other << (B ? kXzTileBits : kXzTileBits + a));
-  }
-  __device__ __forceinline__ uint32_t operator()(uint32_t tau) const {
-    return ((tau >> lrb) << gshift) | fixed | (tau & lrm);
-  }
-};
 
 // The strided passes of split segments (ops of launch_xz_split), in place.
 template <typename T, int OP>
@@ -1238,13 +1273,12 @@ __global__ __launch_bounds__(kBlock) void k_xz_split(const Seg* __restrict__ seg
   if (sg.mode != MODE_PLAIN && sg.stepc[0] > sg.k) return;
   const uint64_t pstride = (uint64_t)1 << sg.nbits;
   constexpr bool B = OP == 1 || OP == 3;
-  const SplitRows row_of(sg.nbits, B, (uint32_t)t.rtile);
+  const XzRows row_of = split_rows(sg.nbits, B, (uint32_t)t.rtile);
   V* buf = (V*)(OP == 2 || OP == 3 ? sg.Y : sg.R) + (uint64_t)t.panel0 * pstride;
   const V* src = OP == 4 ? (const V*)sg.Q + (uint64_t)t.panel0 * pstride : buf;
-  const uint32_t l = threadIdx.x;
   V v[kXzRegs];
 #pragma unroll
-  for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_nt(src, row_of(xz_tau(0, l, q)));
+  for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_nt(src, row_of(0, q));
   double qf[W];
 #pragma unroll
   for (int e = 0; e < W; ++e) qf[e] = 0.0;
@@ -1255,7 +1289,7 @@ __global__ __launch_bounds__(kBlock) void k_xz_split(const Seg* __restrict__ seg
     for (int q = 0; q < kXzRegs; ++q) v[q] = T(1 << kXzTileBits) * v[q];
   }
 #pragma unroll
-  for (int q = 0; q < kXzRegs; ++q) stg_stream<true>(buf, row_of(xz_tau(0, l, q)), v[q]);
+  for (int q = 0; q < kXzRegs; ++q) stg_stream<true>(buf, row_of(0, q), v[q]);
 }
 
 // Plain transform apply Y = H X (MODE_PLAIN segments), H = D_Z + W D_X W:
@@ -1279,6 +1313,7 @@ __global__ __launch_bounds__(kBlock) void k_apply_xz(const Seg* __restrict__ seg
   const V* ub = (const V*)sg.Q + (uint64_t)t.panel0 * pstride;
   V* rb = (V*)sg.R + (uint64_t)t.panel0 * pstride;
   const uint32_t l = threadIdx.x;
+  auto crow = [&](int q) { return XRow{t.row0 + (uint32_t)q * kBlock, l}; };  // contiguous tiles
   V v[kXzRegs];
 
   if (PHASE >= 6) {
@@ -1293,33 +1328,33 @@ __global__ __launch_bounds__(kBlock) void k_apply_xz(const Seg* __restrict__ seg
     if (PHASE == 6 || PHASE == 9) {
       // 6: Y = W_lo T X;  9: Y = W_lo T W_lo X^ / 64 (= W_lo T X, X kept as X^)
 #pragma unroll
-      for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_nt(ub, t.row0 + xz_tau(0, l, q));
+      for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_nt(ub, crow(q));
       if (PHASE == 9) xz_low_transform(v, lds);
       yy_twist<T>(v, t.row0, PHASE == 9 ? T(1) / T(1 << (kXzTileBits / 2)) : T(1));
       xz_low_transform(v, lds);
 #pragma unroll
-      for (int q = 0; q < kXzRegs; ++q) stg_stream<true>(yb, t.row0 + xz_tau(0, l, q), v[q]);
+      for (int q = 0; q < kXzRegs; ++q) stg_stream<true>(yb, crow(q), v[q]);
       return;
     }
     // 8: R += T W_lo Y;  10: R += W_lo T W_lo Y / 64
 #pragma unroll
-    for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_nt((const V*)yb, t.row0 + xz_tau(0, l, q));
+    for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_nt((const V*)yb, crow(q));
     xz_low_transform(v, lds);
     yy_twist<T>(v, t.row0, PHASE == 10 ? T(1) / T(1 << (kXzTileBits / 2)) : T(1));
     if (PHASE == 10) xz_low_transform(v, lds);
 #pragma unroll
     for (int q = 0; q < kXzRegs; ++q) {
-      const uint32_t row = t.row0 + xz_tau(0, l, q);
+      const XRow row = crow(q);
       stg_stream<true>(rb, row, ldg_nt((const V*)rb, row) + v[q]);
     }
   } else if (PHASE == 3) {
     // contiguous tile, in place on X
 #pragma unroll
-    for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_nt(ub, t.row0 + xz_tau(0, l, q));
+    for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_nt(ub, crow(q));
     xz_low_transform(v, lds);
     const T sc = T(1) / T(1 << (kXzTileBits / 2));
 #pragma unroll
-    for (int q = 0; q < kXzRegs; ++q) stg((V*)ub, t.row0 + xz_tau(0, l, q), sc * v[q]);
+    for (int q = 0; q < kXzRegs; ++q) stg((V*)ub, crow(q), sc * v[q]);
   } else if (PHASE == 5) {
     // contiguous tile: the diagonal term in the transformed basis
     const T* dg = (const T*)sg.diag;
@@ -1327,7 +1362,7 @@ __global__ __launch_bounds__(kBlock) void k_apply_xz(const Seg* __restrict__ seg
     T d[kXzRegs];
 #pragma unroll
     for (int q = 0; q < kXzRegs; ++q) {
-      const uint32_t row = t.row0 + xz_tau(0, l, q);
+      const XRow row = crow(q);
       v[q] = ldg_nt(ub, row);
       w[q] = ldg_nt((const V*)rb, row);
       d[q] = ldg_s(dg, row);
@@ -1338,12 +1373,12 @@ __global__ __launch_bounds__(kBlock) void k_apply_xz(const Seg* __restrict__ seg
     xz_low_transform(v, lds);
     const T inv_l = T(1) / T(1 << kXzTileBits);
 #pragma unroll
-    for (int q = 0; q < kXzRegs; ++q) stg_stream<true>(rb, t.row0 + xz_tau(0, l, q), inv_l * v[q] + w[q]);
+    for (int q = 0; q < kXzRegs; ++q) stg_stream<true>(rb, crow(q), inv_l * v[q] + w[q]);
   } else if (PHASE == 0 || PHASE == 2) {
     // contiguous tile: row = row0 + tau; arrangement 0 loads and stores coalesced
     const V* src = PHASE == 0 ? ub : (const V*)rb;
 #pragma unroll
-    for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_nt(src, t.row0 + xz_tau(0, l, q));
+    for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_nt(src, crow(q));
     // phase 2: the diagonal term's operands are loaded while the tile is transformed
     V u[PHASE == 2 ? kXzRegs : 1];
     T d[PHASE == 2 ? kXzRegs : 1];
@@ -1351,39 +1386,34 @@ __global__ __launch_bounds__(kBlock) void k_apply_xz(const Seg* __restrict__ seg
       const T* dg = (const T*)sg.diag;
 #pragma unroll
       for (int q = 0; q < kXzRegs; ++q) {
-        u[q] = ldg_nt(ub, t.row0 + xz_tau(0, l, q));
-        d[q] = ldg_s(dg, t.row0 + xz_tau(0, l, q));
+        u[q] = ldg_nt(ub, crow(q));
+        d[q] = ldg_s(dg, crow(q));
       }
     }
     xz_low_transform(v, lds);
 #pragma unroll
     for (int q = 0; q < kXzRegs; ++q)
-      stg_stream<PHASE != 0>(rb, t.row0 + xz_tau(0, l, q), PHASE == 0 ? v[q] : d[q] * u[q] + v[q]);
+      stg_stream<PHASE != 0>(rb, crow(q), PHASE == 0 ? v[q] : d[q] * u[q] + v[q]);
   } else {
     // strided tile: tau = hi * Lr + lr  ->  row = hi * 4096 + rt * Lr + lr,
     // hb = N - 12 high bits (4 <= hb <= 8 shallow, 9 <= hb <= 12 DEEP;
     // operators go up to kXzMaxBits), Lr = 2^(12 - hb) >= 1
     if (xz_geom(sg.nbits) != (DEEP ? XG_DEEP : XG_SHALLOW)) return;
-    const int hb = sg.nbits - kXzTileBits;
-    const int lrb = kXzTileBits - hb;
-    const uint32_t lrm = (1u << lrb) - 1u;
-    const uint32_t base = (uint32_t)t.rtile << lrb;
-    auto row_of = [&](uint32_t tau) -> uint32_t {
-      return ((tau >> lrb) << kXzTileBits) | (base + (tau & lrm));
-    };
+    const XzRows row_of = strided_rows(sg.nbits, (uint32_t)t.rtile);
+    const int lrb = row_of.lrb;
     // phase 1 transforms R in place; phase 4 reads X^ and scales by L
     const V* src = PHASE == 4 ? ub : (const V*)rb;
     auto run = [&](auto nt_tag) {
       constexpr bool NT = decltype(nt_tag)::value;
 #pragma unroll
-      for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_sel<NT>(src, row_of(xz_tau(0, l, q)));
+      for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_sel<NT>(src, row_of(0, q));
       xz_high_transform<DEEP>(v, lds, (const T*)sg.dx, t.rtile, lrb, row_of);
       if (PHASE == 4) {
 #pragma unroll
         for (int q = 0; q < kXzRegs; ++q) v[q] = T(1 << kXzTileBits) * v[q];
       }
 #pragma unroll
-      for (int q = 0; q < kXzRegs; ++q) stg_sel<NT>(rb, row_of(xz_tau(0, l, q)), v[q]);
+      for (int q = 0; q < kXzRegs; ++q) stg_sel<NT>(rb, row_of(0, q), v[q]);
     };
     if (!DEEP || lrb >= 3) run(std::true_type{});
     else run(std::false_type{});
@@ -1410,7 +1440,11 @@ __global__ __launch_bounds__(kBlock) void k_apply_xz(const Seg* __restrict__ seg
 // FP64 steps move the recurrence (ZR below): pass 2 only leaves
 // Z = W_lo D_Z u_j in Y, pass 1 of the next step starts from
 // s L R + s Z - (beta s) u~_{j-1}, and <u_j, r_j> comes from the XP_* planes.
-// Passes 3-5: the YY part (below).
+// Passes 3-6: the YY part (below).  Pass 6 (FP32, segments with a YY part) is
+// pass 5 followed by pass 2 on the same tile, the sum of pass 5 staying in
+// registers: 5 streams instead of 7.  Its second half's loads come after the
+// first half's transforms, so it needs pass 2's registers (252, two waves a
+// SIMD); on 2^23 rows x 32 columns 977 us against 592 + 757.
 // boff offsets blockIdx.x in the segments' transform tile numbering.
 // ---------------------------------------------------------------------------
 template <typename T, int PASS, bool REGEN, int GEOM>
@@ -1432,10 +1466,11 @@ __global__ __launch_bounds__(kBlock) void k_xz_lanczos(const Seg* __restrict__ s
   const CONST_AS CSeg& sg = cseg(segs, t.seg);
   // pass 1 comes in variants (the regeneration pass needs more registers;
   // one per strided geometry); each leaves the other variants' tiles alone.
-  // Passes 3, 4 and 5 run on the segments with a YY part only (pass 4:
+  // Passes 3 to 6 run on the segments with a YY part only (pass 4:
   // shallow and deep; split segments take launch_xz_split).
   if (PASS == 1 && ((sg.mode == MODE_REGEN) != REGEN || xz_geom(sg.nbits) != GEOM)) return;
-  if ((PASS == 3 || PASS == 4 || PASS == 5) && !sg.xy) return;
+  if ((PASS == 3 || PASS == 4 || PASS == 5 || PASS == 6) && !sg.xy) return;
+  if (PASS == 2 && !ZR && sg.xy) return;   // pass 6
   if (PASS == 4 && xz_geom(sg.nbits) != GEOM) return;
   const int j = PASS == 0 ? 1 : sg.stepc[0];
   if (j > sg.k) return;
@@ -1446,6 +1481,7 @@ __global__ __launch_bounds__(kBlock) void k_xz_lanczos(const Seg* __restrict__ s
   V* rb = (V*)sg.R + (uint64_t)t.panel0 * pstride;
   const V* uprev = j > 1 ? (const V*)slot_ptr<T>(sg, j - 1) + (uint64_t)t.panel0 * pstride : nullptr;
   const T inv_l = T(1) / T(1 << kXzTileBits);
+  auto crow = [&](int q) { return XRow{t.row0 + (uint32_t)q * kBlock, l}; };  // contiguous tiles
   V v[kXzRegs];
 
   if (PASS == 0) {
@@ -1458,23 +1494,17 @@ __global__ __launch_bounds__(kBlock) void k_xz_lanczos(const Seg* __restrict__ s
                                  t.panel0 * W + e, sg.C, amp);
     xz_low_transform(v, lds);
 #pragma unroll
-    for (int q = 0; q < kXzRegs; ++q) stg_stream<true>(rb, t.row0 + xz_tau(0, l, q), v[q]);
+    for (int q = 0; q < kXzRegs; ++q) stg_stream<true>(rb, crow(q), v[q]);
     return;
   }
 
   if (PASS == 1) {
     // strided tile: tau = hi * Lr + lr  ->  row = hi * 4096 + rt * Lr + lr,
     // hb = N - 12 high bits (4 <= hb <= 8 shallow, 9 <= hb <= 10 DEEP),
-    // Lr = 2^(12 - hb) >= 4; split segments: a tile of group A (SplitRows)
-    const int hb = sg.nbits - kXzTileBits;
-    const SplitRows srows(sg.nbits, false, (uint32_t)t.rtile);
-    const int lrb = GEOM == XG_SPLIT ? srows.lrb : kXzTileBits - hb;
-    const uint32_t lrm = (1u << lrb) - 1u;
-    const uint32_t base = (uint32_t)t.rtile << lrb;
-    auto row_of = [&](uint32_t tau) -> uint32_t {
-      if constexpr (GEOM == XG_SPLIT) return srows(tau);
-      else return ((tau >> lrb) << kXzTileBits) | (base + (tau & lrm));
-    };
+    // Lr = 2^(12 - hb) >= 4; split segments: a tile of group A
+    const XzRows row_of = GEOM == XG_SPLIT ? split_rows(sg.nbits, false, (uint32_t)t.rtile)
+                                           : strided_rows(sg.nbits, (uint32_t)t.rtile);
+    const int lrb = row_of.lrb;
     auto run = [&](auto nt_tag) {
       constexpr bool NT = decltype(nt_tag)::value;
       V* ucur = (V*)slot_ptr<T>(sg, j) + (uint64_t)t.panel0 * pstride;
@@ -1482,7 +1512,7 @@ __global__ __launch_bounds__(kBlock) void k_xz_lanczos(const Seg* __restrict__ s
 #pragma unroll
       for (int e = 0; e < W; ++e) acur[e] = (T)st[ST_ACUR * cp + t.panel0 * W + e];
 #pragma unroll
-      for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_sel<NT>((const V*)rb, row_of(xz_tau(0, l, q)));
+      for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_sel<NT>((const V*)rb, row_of(0, q));
       // dsum: |u~_j|^2; XD: dsum[W + e] = <u~_j, u~_{j-1}>
       double dsum[XD ? 2 * W : W];
 #pragma unroll
@@ -1497,7 +1527,7 @@ __global__ __launch_bounds__(kBlock) void k_xz_lanczos(const Seg* __restrict__ s
         const V* upp = j > 2 ? (const V*)slot_ptr<T>(sg, j - 2) + (uint64_t)t.panel0 * pstride : nullptr;
 #pragma unroll
         for (int q = 0; q < kXzRegs; ++q) {
-          const uint32_t row = row_of(xz_tau(0, l, q));
+          const XRow row = row_of(0, q);
           V w = scl * v[q];
           if (upp) {
             const V u2 = ldg_sel<NT>(upp, row);
@@ -1512,7 +1542,7 @@ __global__ __launch_bounds__(kBlock) void k_xz_lanczos(const Seg* __restrict__ s
       if (uprev) {
 #pragma unroll
         for (int q = 0; q < kXzRegs; ++q) {
-          const V up = ldg_sel<NT>(uprev, row_of(xz_tau(0, l, q)));
+          const V up = ldg_sel<NT>(uprev, row_of(0, q));
 #pragma unroll
           for (int e = 0; e < W; ++e) {
             v[q][e] = fma_s(-acur[e], up[e], v[q][e]);
@@ -1522,7 +1552,7 @@ __global__ __launch_bounds__(kBlock) void k_xz_lanczos(const Seg* __restrict__ s
       }
 #pragma unroll
       for (int q = 0; q < kXzRegs; ++q) {
-        stg(ucur, row_of(xz_tau(0, l, q)), v[q]);
+        stg(ucur, row_of(0, q), v[q]);
 #pragma unroll
         for (int e = 0; e < W; ++e) dsum[e] += (double)v[q][e] * (double)v[q][e];
       }
@@ -1535,7 +1565,7 @@ __global__ __launch_bounds__(kBlock) void k_xz_lanczos(const Seg* __restrict__ s
           for (int e = 0; e < W; ++e) y[e] = yt[((uint64_t)b * sg.k + (j - 1)) * cp + t.panel0 * W + e];
 #pragma unroll
           for (int q = 0; q < kXzRegs; ++q) {
-            const uint32_t row = row_of(xz_tau(0, l, q));
+            const XRow row = row_of(0, q);
             V old;
             if (j == 1) {
 #pragma unroll
@@ -1568,7 +1598,7 @@ __global__ __launch_bounds__(kBlock) void k_xz_lanczos(const Seg* __restrict__ s
         if (XD) put_plane<W>(sg, XP_QX, t.rtile, t.panel0, qf, red);
       }
 #pragma unroll
-      for (int q = 0; q < kXzRegs; ++q) stg_sel<NT>(rb, row_of(xz_tau(0, l, q)), v[q]);
+      for (int q = 0; q < kXzRegs; ++q) stg_sel<NT>(rb, row_of(0, q), v[q]);
     };
     if (!DEEP || lrb >= 3) run(std::true_type{});
     else run(std::false_type{});
@@ -1580,12 +1610,12 @@ __global__ __launch_bounds__(kBlock) void k_xz_lanczos(const Seg* __restrict__ s
     const V* ub = (const V*)slot_ptr<T>(sg, j) + (uint64_t)t.panel0 * pstride;
     V* yb = (V*)sg.Y + (uint64_t)t.panel0 * pstride;
 #pragma unroll
-    for (int q = 0; q < kXzRegs; ++q) v[q] = ldg(ub, t.row0 + xz_tau(0, l, q));
+    for (int q = 0; q < kXzRegs; ++q) v[q] = ldg(ub, crow(q));
     xz_low_transform(v, lds);
     yy_twist<T>(v, t.row0, T(1) / T(1 << kXzTileBits));
     xz_low_transform(v, lds);
 #pragma unroll
-    for (int q = 0; q < kXzRegs; ++q) stg_stream<true>(yb, t.row0 + xz_tau(0, l, q), v[q]);
+    for (int q = 0; q < kXzRegs; ++q) stg_stream<true>(yb, crow(q), v[q]);
     return;
   }
   if (PASS == 4) {
@@ -1603,13 +1633,13 @@ __global__ __launch_bounds__(kBlock) void k_xz_lanczos(const Seg* __restrict__ s
     // L R = L W_hi D_X W_hi u~_j + W_lo (T W D_Y W T u_j) in R
     const V* yb = (const V*)sg.Y + (uint64_t)t.panel0 * pstride;
 #pragma unroll
-    for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_nt(yb, t.row0 + xz_tau(0, l, q));
+    for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_nt(yb, crow(q));
     xz_low_transform(v, lds);
     yy_twist<T>(v, t.row0, inv_l);
     xz_low_transform(v, lds);
 #pragma unroll
     for (int q = 0; q < kXzRegs; ++q) {
-      const uint32_t row = t.row0 + xz_tau(0, l, q);
+      const XRow row = crow(q);
       stg_stream<true>(rb, row, ldg_nt((const V*)rb, row) + v[q]);
     }
     return;
@@ -1624,7 +1654,7 @@ __global__ __launch_bounds__(kBlock) void k_xz_lanczos(const Seg* __restrict__ s
     T d[kXzRegs];
 #pragma unroll
     for (int q = 0; q < kXzRegs; ++q) {
-      const uint32_t row = t.row0 + xz_tau(0, l, q);
+      const XRow row = crow(q);
       v[q] = ldg_nt(ub, row);
       d[q] = ldg_s(dg, row);
     }
@@ -1642,18 +1672,35 @@ __global__ __launch_bounds__(kBlock) void k_xz_lanczos(const Seg* __restrict__ s
     xz_low_transform(v, lds);      // W_lo D_Z u
     V* zb = (V*)sg.Y + (uint64_t)t.panel0 * pstride;
 #pragma unroll
-    for (int q = 0; q < kXzRegs; ++q) stg_stream<true>(zb, t.row0 + xz_tau(0, l, q), v[q]);
+    for (int q = 0; q < kXzRegs; ++q) stg_stream<true>(zb, crow(q), v[q]);
     if (XD && sg.mode == MODE_LANCZOS) put_plane<W>(sg, XP_A, t.rtile, t.panel0, d2, red);
     return;
   }
   V w[kXzRegs];
   T d[kXzRegs];
+  if constexpr (PASS == 6) {
+    // the YY part first: w = R + W_lo T W_lo Y / L (pass 5's sum, kept here)
+    const V* yb = (const V*)sg.Y + (uint64_t)t.panel0 * pstride;
 #pragma unroll
-  for (int q = 0; q < kXzRegs; ++q) {
-    const uint32_t row = t.row0 + xz_tau(0, l, q);
-    v[q] = ldg_nt(ub, row);
-    w[q] = ldg_nt((const V*)rb, row);
-    d[q] = ldg_s(dg, row);
+    for (int q = 0; q < kXzRegs; ++q) v[q] = ldg_nt(yb, crow(q));
+    xz_low_transform(v, lds);
+    yy_twist<T>(v, t.row0, inv_l);
+    xz_low_transform(v, lds);
+#pragma unroll
+    for (int q = 0; q < kXzRegs; ++q) w[q] = ldg_nt((const V*)rb, crow(q)) + v[q];
+#pragma unroll
+    for (int q = 0; q < kXzRegs; ++q) {
+      v[q] = ldg_nt(ub, crow(q));
+      d[q] = ldg_s(dg, crow(q));
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < kXzRegs; ++q) {
+      const XRow row = crow(q);
+      v[q] = ldg_nt(ub, row);
+      w[q] = ldg_nt((const V*)rb, row);
+      d[q] = ldg_s(dg, row);
+    }
   }
   const V sc = scur_of<T, 1>(st, cp, t.panel0, 0, false);
   const V scl = sc * T(1 << kXzTileBits);
@@ -1663,7 +1710,7 @@ __global__ __launch_bounds__(kBlock) void k_xz_lanczos(const Seg* __restrict__ s
     const V bp = bps_of<T, 1>(st, cp, t.panel0, 0);
 #pragma unroll
     for (int q = 0; q < kXzRegs; ++q) {
-      const V up = ldg_nt(uprev, t.row0 + xz_tau(0, l, q));
+      const V up = ldg_nt(uprev, crow(q));
 #pragma unroll
       for (int e = 0; e < W; ++e) w[q][e] = fma_s(-bp[e], up[e], w[q][e]);
     }
@@ -1694,7 +1741,7 @@ __global__ __launch_bounds__(kBlock) void k_xz_lanczos(const Seg* __restrict__ s
     V r;
 #pragma unroll
     for (int e = 0; e < W; ++e) r[e] = fma_s(sc[e], v[q][e], w[q][e]);
-    stg_stream<true>(rb, t.row0 + xz_tau(0, l, q), r);
+    stg_stream<true>(rb, crow(q), r);
   }
   if (!dots) return;
   double dq[W];
@@ -2443,6 +2490,7 @@ hipError_t launch_xz_lanczos(int pass, bool regen, const Seg* segs, int nseg, in
   else if (pass == 4 && geo == XG_DEEP) RDM_XZL(4, false, XG_DEEP);
   else if (pass == 4 && geo == XG_SHALLOW) RDM_XZL(4, false, XG_SHALLOW);
   else if (pass == 5) RDM_XZL(5, false, XG_SHALLOW);
+  else if (pass == 6 && sizeof(T) == 4) RDM_XZL(6, false, XG_SHALLOW);
   else return hipErrorInvalidValue;
 #undef RDM_XZL
   return hipGetLastError();

@@ -460,8 +460,8 @@ rdm_status launch_step(int prec, const Seg* dsegs, int nseg, const Launch& L, in
       for (int op : {2, 3, 2})
         RDM_HIP(d ? launch_xz_split<double>(op, dsegs, nseg, L.xz, st)
                   : launch_xz_split<float>(op, dsegs, nseg, L.xz, st));
-    RDM_HIP(d ? launch_xz_lanczos<double>(5, false, dsegs, nseg, L.xz, 0, st)
-              : launch_xz_lanczos<float>(5, false, dsegs, nseg, L.xz, 0, st));
+    // (FP32: in pass 6, with pass 2)
+    if (d) RDM_HIP(launch_xz_lanczos<double>(5, false, dsegs, nseg, L.xz, 0, st));
   }
   if (tm) RDM_HIP(tm->xz1.mark(st));
   RDM_HIP(launch_red_beta(dsegs, nseg, cmax, st));
@@ -472,6 +472,7 @@ rdm_status launch_step(int prec, const Seg* dsegs, int nseg, const Launch& L, in
             : launch_apply_wide<float>(dsegs, nseg, L.wide, L.wsplit, st));
   RDM_HIP(d ? launch_xz_lanczos<double>(2, false, dsegs, nseg, L.xz, 0, st)
             : launch_xz_lanczos<float>(2, false, dsegs, nseg, L.xz, 0, st));
+  if (!d && L.any_xy()) RDM_HIP(launch_xz_lanczos<float>(6, false, dsegs, nseg, L.xz, 0, st));
   if (tm) RDM_HIP(tm->apply.mark(st));
   RDM_HIP(launch_red_alpha(dsegs, nseg, cmax, st));
   return RDM_OK;
