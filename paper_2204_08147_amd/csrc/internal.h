@@ -82,6 +82,13 @@ constexpr int kWideFat = 2;        // partner tiles read by at least two hops go
 // (tile index q * kWideBlock + wave * 64 + lane).
 enum { WT_Q = 0, WT_WAVE = WT_Q + kWideRows, WT_LANE = WT_WAVE + kWideBlock / 64, WT_COUNT = WT_LANE + 64 };
 
+// Hop-table segments of at most 2^kSmallBits rows run all their steps in one
+// launch (k_small): one workgroup per panel, kSmallBlock lanes.
+constexpr int kSmallBits = 11;     // 32 KB of LDS for u_j, up to eight rows per lane
+constexpr int kSmallBlock = 256;
+constexpr int kSmallRows = (1 << kSmallBits) / kSmallBlock;
+constexpr int kSmallHops = kSmallBits * (kSmallBits + 1) / 2;  // every pair and every site
+
 // One off-diagonal term of H as the apply sees it: row idx couples to the
 // partner idx ^ f with coefficient c = (parity(idx & m) == 0) ? cs : cd.
 // f is split into the bits above the 256-row tile (fhi, shared by the hop's
@@ -264,6 +271,10 @@ hipError_t launch_apply(const Seg* segs, int nseg, int ntiles, int slab, hipStre
 // many workgroups (the other one 0)
 template <typename T>
 hipError_t launch_apply_wide(const Seg* segs, int nseg, int ntiles, int nsplit, hipStream_t st);
+// every step of the small segments segs[0 .. nseg) (start block, recurrences
+// and histories; MODE_LANCZOS or MODE_REGEN); npanels = their panels
+template <typename T>
+hipError_t launch_small(const Seg* segs, int nseg, int npanels, hipStream_t st);
 // pass 0, 1 or 2 of the plain transform apply Y = H X (MODE_PLAIN segments
 // with xz = 1); passes 3 (once: X^ = W_lo X / 64 in place), 4 and 5 the same
 // product on blocks kept as X^, giving R = W_lo H X / 64; the strided pass
@@ -319,6 +330,7 @@ constexpr int kTriRows = 4;                  // rows of T per lane at most
 constexpr int kTriMaxK = 64 * kTriRows;
 constexpr int kTriBetas = 16;                // temperatures per launch
 constexpr int kTriMaxTerms = 4000;
+constexpr int kTriMaxBits = 20;
 // Lanczos coefficients of one segment ([k][cpad]) and its Krylov sizes
 struct TriSeg {
   const double *ha, *hb, *hs;

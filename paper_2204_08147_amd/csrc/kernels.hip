@@ -192,10 +192,11 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double* lds, double* 
 // The same for NV = a power of two up to 64 values, folding the values as the
 // lanes combine: at each of the first log2 NV exchanges a lane hands over the
 // half of its values that its partner goes on with, so a wave takes NV - 1 +
-// (6 - log2 NV) exchanges instead of 6 NV.  Threads 0..NV-1 receive the totals.
-template <int NV, int O = 1, int N = NV>
+// (6 - log2 NV) exchanges instead of 6 NV.  Each value is summed in wave_sum's
+// order.  Threads 0..NV-1 receive the totals.
+template <int NV, int O = 32, int N = NV>
 __device__ __forceinline__ void wave_fold(double (&v)[NV], int lane) {
-  if constexpr (O < 64) {
+  if constexpr (O > 0) {
     if constexpr (N > 1) {
       constexpr int H = N / 2;
       const bool up = (lane & O) != 0;     // these lanes keep the upper half
@@ -204,25 +205,22 @@ __device__ __forceinline__ void wave_fold(double (&v)[NV], int lane) {
         const double keep = up ? v[i + H] : v[i], give = up ? v[i] : v[i + H];
         v[i] = keep + __shfl_xor(give, O, 64);
       }
-      wave_fold<NV, 2 * O, H>(v, lane);
+      wave_fold<NV, O / 2, H>(v, lane);
     } else {
       v[0] += __shfl_xor(v[0], O, 64);
-      wave_fold<NV, 2 * O, 1>(v, lane);
+      wave_fold<NV, O / 2, 1>(v, lane);
     }
   }
 }
+// after wave_fold<NV>: the value a lane holds (the lanes' highest bits)
+template <int NV>
+__device__ __forceinline__ int fold_index(int lane) { return lane / (64 / NV); }
 template <int NV>
 __device__ __forceinline__ void block_sum_fold(double (&v)[NV], double* lds, double* tot) {
   static_assert(NV <= 64 && (NV & (NV - 1)) == 0, "a power of two of at most one value per lane");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   wave_fold(v, lane);
-  // lane bits 0 .. log2 NV - 1 hold the value's index, its highest bit first
-  if (lane < NV) {
-    int idx = 0;
-#pragma unroll
-    for (int b = 1, h = NV >> 1; h > 0; b <<= 1, h >>= 1) idx |= (lane & b) ? h : 0;
-    lds[wave * NV + idx] = v[0];
-  }
+  if (lane % (64 / NV) == 0) lds[wave * NV + fold_index<NV>(lane)] = v[0];
   __syncthreads();
   if (threadIdx.x < NV) {
     const int t = threadIdx.x;
@@ -2216,6 +2214,228 @@ __global__ __launch_bounds__(kBlock) void k_red_alpha(const Seg* __restrict__ se
 }
 
 // ---------------------------------------------------------------------------
+// All k steps of a small hop-table segment (up to kSmallBits sites) in one
+// launch: columns are independent, so a workgroup owns one panel and keeps its
+// vectors for the whole run -- u_j in LDS (the gathers of the product), u_j,
+// u_{j-1} and r in registers -- and the reductions of a step stay inside it.
+// Launched one kernel per phase, a step of a ten-spin chain is 4 launches of
+// 3-5 us that leave the chip idle; here it is two barriers and two sums, 3.4 us
+// (1 + 9 sites, FP64, 8 columns: 30 steps 470 -> 102 us; with 1024 lanes of one
+// row instead of 256 of four 168 us: the sums and the hops' latency set it).
+// The order of the hops of a row is k_apply's, the rounding order of the
+// recurrence k_norm's and k_apply's and that of the sums the reductions', so
+// the results are those of the kernel-per-phase steps bit for bit.
+// ---------------------------------------------------------------------------
+// Totals of the R * W values v[r * W + e] of tile r (row r * kSmallBlock +
+// lane) and column e, over lanes and tiles, in every lane: a tile's sum in
+// block_sum's order, the tiles in column_total's tree, so the sums are those of
+// the kernel-per-phase steps bit for bit.
+template <int R, int W>
+__device__ __forceinline__ void small_totals(double (&v)[R * W], double* red, double (&tot)[W]) {
+  constexpr int NV = R * W;
+  static_assert(kSmallBlock == kBlock && NV <= 64, "one tile per row of a lane, one value per lane");
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  wave_fold(v, lane);
+  if (lane % (64 / NV) == 0) red[wave * NV + fold_index<NV>(lane)] = v[0];
+  __syncthreads();
+  const int i = lane % NV;
+  double x = ((red[i] + red[NV + i]) + red[2 * NV + i]) + red[3 * NV + i];
+#pragma unroll
+  for (int o = R / 2; o > 0; o >>= 1) x += __shfl_xor(x, o * W, 64);
+#pragma unroll
+  for (int e = 0; e < W; ++e) tot[e] = __shfl(x, e, 64);
+}
+
+// R rows per lane: kSmallBlock lanes cover the segment.
+template <typename T, int R>
+__device__ __forceinline__ void small_run(const CONST_AS CSeg& sg, int panel, typename PanelT<T>::V* tl, GHop<T>* hop,
+                                          double (*red)[kSmallBlock / 64 * kSmallRows * PanelT<T>::W]) {
+  using V = typename PanelT<T>::V;
+  constexpr int W = PanelT<T>::W;
+  const int cp = sg.cpad, kk = sg.k;
+  const uint32_t dim = 1u << sg.nbits;
+  const uint64_t pstride = dim;
+  const bool regen = sg.mode == MODE_REGEN;
+  const int lane = threadIdx.x;
+  int nstaged = 0;
+  {
+    const CONST_AS HopGroup* gr = (const CONST_AS HopGroup*)sg.groups;
+    const CONST_AS GHop<T>* hp = (const CONST_AS GHop<T>*)sg.hops;
+    for (int g = 0; g < sg.ngroups; ++g) {
+      const int n = gr[g].n0 + gr[g].n1 + gr[g].n2;
+      for (int i = lane; i < n; i += kSmallBlock) {
+        const CONST_AS GHop<T>& h = hp[gr[g].start + i];
+        hop[nstaged + i] = GHop<T>{h.flo | gr[g].fhi, h.m, h.cs, h.cd};
+      }
+      nstaged += n;
+    }
+    const CONST_AS GHop<T>* th = (const CONST_AS GHop<T>*)sg.thin;
+    const int nt = sg.nt0 + sg.nt1 + sg.nt2;
+    for (int i = lane; i < nt; i += kSmallBlock) hop[nstaged + i] = GHop<T>{th[i].flo, th[i].m, th[i].cs, th[i].cd};
+    nstaged += nt;
+  }
+  const T amp = amp_of<T>(sg.nb);
+  uint32_t row[R];
+  bool on[R];
+  T d[R];
+  V u[R], up[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    row[r] = (uint32_t)(lane + r * kSmallBlock);
+    on[r] = row[r] < dim;
+    d[r] = on[r] ? ldg_s((const T*)sg.diag, row[r]) : T(0);
+#pragma unroll
+    for (int e = 0; e < W; ++e) {
+      u[r][e] = on[r] ? start_value<T>(sg.start_kind, sg.ns_log, sg.nb, sg.seed, row[r], panel * W + e, sg.C, amp) : T(0);
+      up[r][e] = T(0);
+    }
+  }
+  // the column scalars of k_red_beta / k_red_alpha, the same in every lane
+  double scur[W], runmax[W];
+  bool frozen[W];
+  int kc[W];
+#pragma unroll
+  for (int e = 0; e < W; ++e) {
+    scur[e] = runmax[e] = 0.0;
+    frozen[e] = panel * W + e >= sg.C;
+    kc[e] = frozen[e] ? 0 : kk;
+  }
+  const bool head = lane == 0;
+  const int c0 = panel * W;
+  for (int j = 1; j <= kk; ++j) {
+    double v[R * W], tot[W];
+#pragma unroll
+    for (int i = 0; i < R * W; ++i) v[i] = 0.0;
+    V* slot = sg.ring ? nullptr : (V*)slot_ptr<T>(sg, j) + (uint64_t)panel * pstride;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (!on[r]) continue;
+      tl[row[r]] = u[r];
+      if (slot) stg(slot, row[r], u[r]);
+#pragma unroll
+      for (int e = 0; e < W; ++e) v[r * W + e] = (double)u[r][e] * (double)u[r][e];
+      if (regen) {
+        const CONST_AS T* yt = (const CONST_AS T*)sg.ytab;
+        for (int b = 0; b < sg.n_beta; ++b) {
+          V* pb = (V*)sg.psi + (uint64_t)b * (sg.blk / W) + (uint64_t)panel * pstride;
+          V x;
+#pragma unroll
+          for (int e = 0; e < W; ++e) x[e] = T(0);
+          if (j > 1) x = ldg((const V*)pb, row[r]);
+#pragma unroll
+          for (int e = 0; e < W; ++e) x[e] = fma_s(yt[((uint64_t)b * kk + (j - 1)) * cp + c0 + e], u[r][e], x[e]);
+          stg(pb, row[r], x);
+        }
+      }
+    }
+    small_totals<R, W>(v, red[0], tot);
+    V sc, bp;
+#pragma unroll
+    for (int e = 0; e < W; ++e) {
+      const uint64_t at = (uint64_t)(j - 1) * cp + c0 + e;
+      double s, beff;
+      if (regen) {
+        s = sg.h_s[at];
+        beff = j == 1 ? 0.0 : sg.h_beta[at - cp];
+      } else if (j == 1) {
+        beff = 0.0;
+        s = frozen[e] ? 0.0 : 1.0 / sqrt(tot[e]);
+      } else {
+        const double b = sqrt(tot[e]);
+        if (frozen[e]) {
+          beff = s = 0.0;
+        } else if (!(b > sg.tau * runmax[e])) {
+          frozen[e] = true;
+          kc[e] = j - 1;
+          beff = s = 0.0;
+        } else {
+          runmax[e] = fmax(runmax[e], b);
+          beff = b;
+          s = 1.0 / b;
+        }
+        if (head) sg.h_beta[at - cp] = beff;
+      }
+      if (!regen && head) sg.h_s[at] = s;
+      const double sprev = j == 1 ? 0.0 : scur[e];
+      sc[e] = (T)s;
+      bp[e] = (T)(beff * sprev);
+      scur[e] = s;
+    }
+    V res[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) res[r] = d[r] * u[r];
+#pragma unroll 4
+    for (int h = 0; h < nstaged; ++h) {
+      const GHop<T> x = hop[h];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        // (rows past dim read inside the buffer and are not used)
+        const T c = (__builtin_popcount(row[r] & x.m) & 1u) ? x.cd : x.cs;
+        res[r] += c * tl[row[r] ^ x.flo];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < R * W; ++i) v[i] = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      res[r] = sc * res[r];
+      if (j > 1) {
+#pragma unroll
+        for (int e = 0; e < W; ++e) res[r][e] = fma_s(-bp[e], up[r][e], res[r][e]);
+      }
+      if (on[r]) {
+#pragma unroll
+        for (int e = 0; e < W; ++e) v[r * W + e] = (double)u[r][e] * (double)res[r][e];
+      }
+    }
+    small_totals<R, W>(v, red[1], tot);
+    V ac;
+#pragma unroll
+    for (int e = 0; e < W; ++e) {
+      const uint64_t at = (uint64_t)(j - 1) * cp + c0 + e;
+      double a;
+      if (regen) {
+        a = sg.h_alpha[at];
+      } else {
+        a = frozen[e] ? 0.0 : scur[e] * tot[e];
+        runmax[e] = fmax(runmax[e], fabs(a));
+        if (head) sg.h_alpha[at] = a;
+      }
+      ac[e] = (T)(a * scur[e]);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      up[r] = u[r];
+#pragma unroll
+      for (int e = 0; e < W; ++e) u[r][e] = fma_s(-ac[e], up[r][e], res[r][e]);
+    }
+  }
+  if (!regen && head) {
+#pragma unroll
+    for (int e = 0; e < W; ++e) sg.kc[c0 + e] = kc[e];
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kSmallBlock) void k_small(const Seg* __restrict__ segs, int nseg) {
+  using V = typename PanelT<T>::V;
+  constexpr int W = PanelT<T>::W;
+  __shared__ V tl[1 << kSmallBits];
+  __shared__ GHop<T> hop[kSmallHops];      // every hop in k_apply's order, flo = all its flip bits
+  __shared__ double red[2][kSmallBlock / 64 * kSmallRows * W];
+  // panel blockIdx.x of the segments in order
+  const CONST_AS Seg* cs = (const CONST_AS Seg*)segs;
+  int si = 0, panel = (int)blockIdx.x;
+  while (si + 1 < nseg && panel >= cs[si].P) panel -= cs[si++].P;
+  const CONST_AS CSeg& sg = cs[si];
+  static_assert(kSmallRows == 8, "rows per lane");
+  if (sg.nbits <= kSmallBits - 3) small_run<T, 1>(sg, panel, tl, hop, red);
+  else if (sg.nbits == kSmallBits - 2) small_run<T, 2>(sg, panel, tl, hop, red);
+  else if (sg.nbits == kSmallBits - 1) small_run<T, 4>(sg, panel, tl, hop, red);
+  else small_run<T, 8>(sg, panel, tl, hop, red);
+}
+
+// ---------------------------------------------------------------------------
 // recombination psi_b = sum_j y'_{b,j} u_j (fused) and the per-bath-vector
 // d_s x d_s Gram blocks, accumulated per lane over its rows in T and summed
 // across lanes / tiles in FP64.
@@ -2424,6 +2644,13 @@ hipError_t launch_apply_wide(const Seg* segs, int nseg, int ntiles, int nsplit, 
 }
 
 template <typename T>
+hipError_t launch_small(const Seg* segs, int nseg, int npanels, hipStream_t st) {
+  if (npanels <= 0) return hipSuccess;
+  hipLaunchKernelGGL((k_small<T>), dim3(npanels), dim3(kSmallBlock), 0, st, segs, nseg);
+  return hipGetLastError();
+}
+
+template <typename T>
 hipError_t launch_xz_split(int op, const Seg* segs, int nseg, int ntiles, hipStream_t st) {
   if (ntiles <= 0) return hipSuccess;
   const dim3 g(ntiles), b(kBlock);
@@ -2606,6 +2833,8 @@ template hipError_t launch_apply<float>(const Seg*, int, int, int, hipStream_t);
 template hipError_t launch_apply<double>(const Seg*, int, int, int, hipStream_t);
 template hipError_t launch_apply_wide<float>(const Seg*, int, int, int, hipStream_t);
 template hipError_t launch_apply_wide<double>(const Seg*, int, int, int, hipStream_t);
+template hipError_t launch_small<float>(const Seg*, int, int, hipStream_t);
+template hipError_t launch_small<double>(const Seg*, int, int, hipStream_t);
 template hipError_t launch_xz_pass<float>(int, const Seg*, int, int, hipStream_t, int);
 template hipError_t launch_xz_split<float>(int, const Seg*, int, int, hipStream_t);
 template hipError_t launch_xz_split<double>(int, const Seg*, int, int, hipStream_t);

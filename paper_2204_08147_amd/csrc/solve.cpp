@@ -588,7 +588,9 @@ rdm_status weights_launch(InstRun& r, hipStream_t st) {
   double bmax = 0.0;
   for (double b : r.betas) bmax = std::max(bmax, b);
   const double zmax = std::max(1.0, 1.01 * bmax * std::max(norm_bound(p.h->op[0]), norm_bound(p.h->op[1])));
-  r.on_device = std::max(p.k, p.kb) <= kTriMaxK && zmax < 1e8 && TriArgs::n_terms(zmax) <= kTriMaxTerms &&
+  // (above 2^kTriMaxBits rows the host takes less than 1 % of a solve: 36
+  // columns on 23 bits 0.5 ms of 690)
+  r.on_device = p.tot.nbits <= kTriMaxBits && std::max(p.k, p.kb) <= kTriMaxK && zmax < 1e8 && TriArgs::n_terms(zmax) <= kTriMaxTerms &&
                 tri_doubles(p) * 8 <= p.o_gseg - p.o_gpart;
   if (!r.on_device) return RDM_OK;
   TriArgs a{};
@@ -865,6 +867,27 @@ rdm_status run_phase(std::vector<Seg>& hsegs, Seg* dsegs, int prec, int phase, h
       set_error("internal: a transform segment that needs the Y block has none");
       return RDM_E_INVALID;
     }
+  // small segments run whole, in one launch, from the tail of the table; the
+  // others step together (all of them when the steps are to be timed)
+  const bool small = !tm && !rt;
+  const auto mid = std::stable_partition(hsegs.begin(), hsegs.end(), [&](const Seg& sg) {
+    return !(small && !sg.xz && !sg.wide && sg.nbits <= kSmallBits);
+  });
+  std::vector<Seg> tail(mid, hsegs.end());
+  hsegs.erase(mid, hsegs.end());
+  if (!tail.empty()) {
+    Seg* dtail = dsegs + hsegs.size();
+    int panels = 0;
+    for (const auto& sg : tail) panels += sg.P;
+    RDM_HIP(hipMemcpyAsync(dtail, tail.data(), tail.size() * sizeof(Seg), hipMemcpyHostToDevice, st));
+    RDM_HIP(prec == RDM_FP64 ? launch_small<double>(dtail, (int)tail.size(), panels, st)
+                             : launch_small<float>(dtail, (int)tail.size(), panels, st));
+    if (hsegs.empty()) {
+      // the host table must outlive the asynchronous copy
+      RDM_HIP(hipStreamSynchronize(st));
+      return RDM_OK;
+    }
+  }
   int kmax = 0, cmax = 0;
   for (const auto& sg : hsegs) {
     kmax = std::max(kmax, sg.k);
