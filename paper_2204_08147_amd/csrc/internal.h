@@ -340,12 +340,13 @@ struct TriSeg {
 // scratch (doubles): smallest eigenvalue and upper bound per column of H_t,
 // the same of H_b, the quadratures [n_beta][b.C] (over |v|^2 = 1 / s_1^2),
 // then kTriOut values {E0, E0b, broken-down columns of H_t, of H_b}
-// (NaN for E0 / E0b when a coefficient is not finite)
+// (NaN for E0 / E0b when a coefficient is not finite), then, when yt is null,
+// the quadratures [n_beta][t.C] of H_t's columns
 constexpr int kTriOut = 4;
 struct TriArgs {
   TriSeg t, b;
   double* scratch;
-  void* yt;                                  // [n_beta][t.k][t.cpad] in T
+  void* yt;                                  // [n_beta][t.k][t.cpad] in T, or null
   double bscale;                             // factor of the weights
   int32_t n_beta, beta0, max_terms;
   double beta[kTriBetas];

@@ -12,8 +12,8 @@
 // The hot-path kernels run Lanczos on the n_v product columns (H_t) and the
 // n_v bath vectors (H_b) in one launch sequence; each column's T gives the
 // Gauss quadrature e_1^T exp(-beta (T - E0)) e_1 (eqn:fT with block size one),
-// with E0 the smallest Ritz value over the columns (overflow shift), on the
-// host.
+// with E0 the smallest Ritz value over the columns (overflow shift): on the
+// device where its range allows (solve.h), else on the host.
 #include <algorithm>
 #include <cmath>
 
@@ -58,23 +58,17 @@ double log_mean_exp(const double* x, int n) {
   return m + std::log(s / n);
 }
 
-rdm_status product_run(const ProductPlan& pp, const rdm_hamiltonian* h, const double* betas, int n_beta,
-                       uint64_t seed, double tau, bool graph, char* ws, hipStream_t st,
-                       rdm_product_result* out) {
-  const OpDevice *op_t = nullptr, *op_b = nullptr;
-  rdm_status s = get_device_op(h, 0, pp.prec, st, &op_t);
-  if (s == RDM_OK) s = get_device_op(h, 1, pp.prec, st, &op_b);
-  if (s != RDM_OK) return s;
-  char* base = ws + pp.header;
-  std::vector<Seg> segs{make_plain_seg(pp.tot, op_t, base, MODE_LANCZOS, START_PRODUCT, h->n_s, h->n_b, seed, tau),
-                        make_plain_seg(pp.bath, op_b, base, MODE_LANCZOS, START_BATH, 0, h->n_b, seed, tau)};
-  if ((s = run_phase(segs, (Seg*)ws, pp.prec, 0, st, nullptr, true, graph)) != RDM_OK) return s;
+// The quadratures e_1^T exp(-beta (T - E0)) e_1 over s_1^2 (x^T f(H) x = |x|^2
+// e_1^T f(T) e_1, |x| = 1 / s_1, unit up to rounding) and the shifts, on the host.
+rdm_status host_quadratures(const ProductPlan& pp, char* base, const double* betas, int n_beta, hipStream_t st,
+                            std::vector<double>& qt, std::vector<double>& qb, double& e0, double& e0b) {
+  rdm_status s;
+  const int n_v = pp.n_v;
   std::vector<double> ta, tb, tsc, ba, bb, bsc;
   std::vector<int32_t> tkc, bkc;
   if ((s = fetch_history(pp.tot, base, ta, tb, tsc, tkc, st)) != RDM_OK) return s;
   if ((s = fetch_history(pp.bath, base, ba, bb, bsc, bkc, st)) != RDM_OK) return s;
   RDM_HIP(hipStreamSynchronize(st));
-  const int n_v = pp.n_v;
   std::vector<TridiagEig> et(n_v), eb(n_v);
   parallel_jobs(2 * n_v, [&](int t) {
     const bool bath = t >= n_v;
@@ -88,7 +82,7 @@ rdm_status product_run(const ProductPlan& pp, const rdm_hamiltonian* h, const do
     for (int j = 0; j + 1 < kk; ++j) be[j] = b[(size_t)j * stride + c];
     (bath ? eb : et)[c].solve(al.data(), be.data(), kk);
   });
-  double e0 = INFINITY, e0b = INFINITY;
+  e0 = e0b = INFINITY;
   for (int c = 0; c < n_v; ++c) {
     if (!et[c].ok || !eb[c].ok || et[c].n == 0 || eb[c].n == 0) {
       set_error("tridiagonal eigenproblem failed");
@@ -97,18 +91,66 @@ rdm_status product_run(const ProductPlan& pp, const rdm_hamiltonian* h, const do
     for (double x : et[c].theta) e0 = std::min(e0, x);
     for (double x : eb[c].theta) e0b = std::min(e0b, x);
   }
+  for (int bi = 0; bi < n_beta; ++bi)
+    for (int c = 0; c < n_v; ++c) {
+      const double beta = betas[bi];
+      double wt = 0.0, wb = 0.0;
+      for (int q = 0; q < et[c].n; ++q) wt += et[c].zrow[q] * et[c].zrow[q] * std::exp(-beta * (et[c].theta[q] - e0));
+      for (int q = 0; q < eb[c].n; ++q) wb += eb[c].zrow[q] * eb[c].zrow[q] * std::exp(-beta * (eb[c].theta[q] - e0b));
+      qt[(size_t)bi * n_v + c] = wt / (tsc[c] * tsc[c]);
+      qb[(size_t)bi * n_v + c] = wb / (bsc[c] * bsc[c]);
+    }
+  return RDM_OK;
+}
+
+rdm_status product_run(const ProductPlan& pp, const rdm_hamiltonian* h, const double* betas, int n_beta,
+                       uint64_t seed, double tau, bool graph, char* ws, hipStream_t st,
+                       rdm_product_result* out) {
+  const OpDevice *op_t = nullptr, *op_b = nullptr;
+  rdm_status s = get_device_op(h, 0, pp.prec, st, &op_t);
+  if (s == RDM_OK) s = get_device_op(h, 1, pp.prec, st, &op_b);
+  if (s != RDM_OK) return s;
+  char* base = ws + pp.header;
+  std::vector<Seg> segs{make_plain_seg(pp.tot, op_t, base, MODE_LANCZOS, START_PRODUCT, h->n_s, h->n_b, seed, tau),
+                        make_plain_seg(pp.bath, op_b, base, MODE_LANCZOS, START_BATH, 0, h->n_b, seed, tau)};
+  if ((s = run_phase(segs, (Seg*)ws, pp.prec, 0, st, nullptr, true, graph)) != RDM_OK) return s;
+  const int n_v = pp.n_v;
+  // quadratures over |x|^2 and the shifts
+  std::vector<double> qt((size_t)n_beta * n_v), qb((size_t)n_beta * n_v);
+  double e0 = INFINITY, e0b = INFINITY, bmax = 0.0, zmax = 0.0;
+  for (int bi = 0; bi < n_beta; ++bi) bmax = std::max(bmax, betas[bi]);
+  // device scratch: the basis slots, which nothing reads any more
+  const size_t nd = 4 * (size_t)n_v + 2 * qt.size() + kTriOut;
+  if (tri_in_range(h, std::max(pp.k, pp.kb), bmax, &zmax) && nd * 8 <= pp.tot.o_R - pp.tot.o_Q) {
+    TriArgs a{};
+    a.t = tri_seg(pp.tot, base);
+    a.b = tri_seg(pp.bath, base);
+    a.scratch = (double*)(base + pp.tot.o_Q);
+    a.n_beta = n_beta;
+    RDM_HIP(pp.prec == RDM_FP64 ? launch_tri<double>(a, betas, n_beta, zmax, st)
+                                : launch_tri<float>(a, betas, n_beta, zmax, st));
+    std::vector<double> v(nd);
+    RDM_HIP(hipMemcpyAsync(v.data(), a.scratch, nd * 8, hipMemcpyDeviceToHost, st));
+    RDM_HIP(hipStreamSynchronize(st));
+    const double* q = v.data() + 4 * n_v;
+    e0 = q[qb.size()];
+    e0b = q[qb.size() + 1];
+    if (!std::isfinite(e0) || !std::isfinite(e0b)) {
+      set_error("tridiagonal eigenproblem failed");
+      return RDM_E_NONFINITE;
+    }
+    std::copy(q, q + qb.size(), qb.begin());
+    std::copy(q + qb.size() + kTriOut, q + qb.size() + kTriOut + qt.size(), qt.begin());
+  } else if ((s = host_quadratures(pp, base, betas, n_beta, st, qt, qb, e0, e0b)) != RDM_OK) {
+    return s;
+  }
   const double ln2 = std::log(2.0);
   std::vector<double> lt(n_v), lb(n_v);
   for (int bi = 0; bi < n_beta; ++bi) {
     const double beta = betas[bi];
     for (int c = 0; c < n_v; ++c) {
-      double wt = 0.0, wb = 0.0;
-      for (int q = 0; q < et[c].n; ++q) wt += et[c].zrow[q] * et[c].zrow[q] * std::exp(-beta * (et[c].theta[q] - e0));
-      for (int q = 0; q < eb[c].n; ++q) wb += eb[c].zrow[q] * eb[c].zrow[q] * std::exp(-beta * (eb[c].theta[q] - e0b));
-      // x^T f(H) x = |x|^2 e_1^T f(T) e_1, |x| = 1 / s_1 (unit up to rounding)
-      const double st1 = tsc[c], sb1 = bsc[c];
-      lt[c] = std::log(wt / (st1 * st1)) - beta * e0 + h->n * ln2;
-      lb[c] = std::log(wb / (sb1 * sb1)) - beta * e0b + h->n_b * ln2;
+      lt[c] = std::log(qt[(size_t)bi * n_v + c]) - beta * e0 + h->n * ln2;
+      lb[c] = std::log(qb[(size_t)bi * n_v + c]) - beta * e0b + h->n_b * ln2;
       if (!std::isfinite(lt[c]) || !std::isfinite(lb[c])) {
         set_error("non-finite quadrature value");
         return RDM_E_NONFINITE;

@@ -581,30 +581,29 @@ double norm_bound(const OpTables& t) {
 
 }  // namespace
 
+bool tri_in_range(const rdm_hamiltonian* h, int k, double beta_max, double* zmax) {
+  // half the width of T's Gershgorin interval is at most 2 |H|, so z =
+  // (beta / 2) * that is at most beta |H| (FP32 recurrences: to rounding).
+  // Above 2^kTriMaxBits rows the host takes less than 1 % of a solve: 36
+  // columns on 23 bits 0.5 ms of 690.
+  *zmax = std::max(1.0, 1.01 * beta_max * std::max(norm_bound(h->op[0]), norm_bound(h->op[1])));
+  return h->n <= kTriMaxBits && k <= kTriMaxK && *zmax < 1e8 && TriArgs::n_terms(*zmax) <= kTriMaxTerms;
+}
+
+TriSeg tri_seg(const SegPlan& g, char* base) {
+  return TriSeg{(const double*)(base + g.o_ha), (const double*)(base + g.o_hb), (const double*)(base + g.o_hs),
+                (const int32_t*)(base + g.o_kc), g.k, g.cpad, g.C};
+}
+
 rdm_status weights_launch(InstRun& r, hipStream_t st) {
   const InstPlan& p = *r.plan;
-  // half the width of T's Gershgorin interval is at most 2 |H|, so z =
-  // (beta / 2) * that is at most beta |H| (FP32 recurrences: to rounding)
-  double bmax = 0.0;
+  double bmax = 0.0, zmax = 0.0;
   for (double b : r.betas) bmax = std::max(bmax, b);
-  const double zmax = std::max(1.0, 1.01 * bmax * std::max(norm_bound(p.h->op[0]), norm_bound(p.h->op[1])));
-  // (above 2^kTriMaxBits rows the host takes less than 1 % of a solve: 36
-  // columns on 23 bits 0.5 ms of 690)
-  r.on_device = p.tot.nbits <= kTriMaxBits && std::max(p.k, p.kb) <= kTriMaxK && zmax < 1e8 && TriArgs::n_terms(zmax) <= kTriMaxTerms &&
-                tri_doubles(p) * 8 <= p.o_gseg - p.o_gpart;
+  r.on_device = tri_in_range(p.h, std::max(p.k, p.kb), bmax, &zmax) && tri_doubles(p) * 8 <= p.o_gseg - p.o_gpart;
   if (!r.on_device) return RDM_OK;
   TriArgs a{};
-  for (int w = 0; w < 2; ++w) {
-    const SegPlan& g = w == 0 ? p.tot : p.bath;
-    TriSeg& s = w == 0 ? a.t : a.b;
-    s.ha = (const double*)(r.base + g.o_ha);
-    s.hb = (const double*)(r.base + g.o_hb);
-    s.hs = (const double*)(r.base + g.o_hs);
-    s.kc = (const int32_t*)(r.base + g.o_kc);
-    s.k = g.k;
-    s.cpad = g.cpad;
-    s.C = g.C;
-  }
+  a.t = tri_seg(p.tot, r.base);
+  a.b = tri_seg(p.bath, r.base);
   a.scratch = tri_scratch(r);
   a.yt = r.base + p.o_y;
   a.bscale = r.op_t->xz ? kXzBasisScale : 1.0;

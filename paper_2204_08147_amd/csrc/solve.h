@@ -155,6 +155,10 @@ int tuned_slab(int prec, std::vector<Seg>& segs);
 // weights_launch enqueues the device kernels when the instance is in their
 // range (then r.on_device); weights_collect waits for them, or does the whole
 // phase on the host.  weights_phase: both.
+// Whether the device takes the exponentials of recurrences of up to k steps at
+// inverse temperatures up to beta_max; zmax: the bound its series are sized for.
+bool tri_in_range(const rdm_hamiltonian* h, int k, double beta_max, double* zmax);
+TriSeg tri_seg(const SegPlan& g, char* base);
 rdm_status weights_launch(InstRun& r, hipStream_t st);
 rdm_status weights_collect(InstRun& r, hipStream_t st);
 rdm_status weights_phase(InstRun& r, hipStream_t st);

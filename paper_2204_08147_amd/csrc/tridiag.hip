@@ -17,7 +17,8 @@
 // columns up to the chip's waves.  On 16 host threads (implicit QR per column,
 // coefficients copied to the host and weights back) 3 x 500 columns with
 // 8 temperatures took 25 ms of a solve, now 0.25 ms; 80 columns with
-// 4 temperatures 1.6 ms, now 0.06 ms; 12 columns with k = 30 0.3 ms, now 0.04.
+// 4 temperatures 1.6 ms, now 0.06 ms; 12 columns with k = 30 0.3 ms, now 0.04;
+// the product-state estimate's 2 x 64 columns (2 + 18 sites) 0.4 ms of 9.3.
 #include "internal.h"
 
 namespace rdm {
@@ -111,8 +112,9 @@ __global__ __launch_bounds__(64) void k_tri_bounds(TriArgs a) {
   }
 }
 
-// The weights (H_t's columns, in the recombination's layout and scaling) and
-// the quadratures (H_b's) of inverse temperature blockIdx.y.
+// The weights (H_t's columns, in the recombination's layout and scaling; the
+// quadratures when there is no place for them) and the quadratures (H_b's) of
+// inverse temperature blockIdx.y.
 template <typename T, int R>
 __global__ __launch_bounds__(64) void k_tri_weights(TriArgs a) {
   extern __shared__ double cf[];           // e^-z I_n(z), n <= N
@@ -120,11 +122,13 @@ __global__ __launch_bounds__(64) void k_tri_weights(TriArgs a) {
   const TriCol col{(int)blockIdx.x >= a.t.cpad, (int)blockIdx.x >= a.t.cpad ? (int)blockIdx.x - a.t.cpad : (int)blockIdx.x};
   const TriSeg& s = col.bath ? a.b : a.t;
   const int c = col.c, cp = s.cpad, ib = a.beta0 + (int)blockIdx.y;
+  const bool weights = !col.bath && a.yt;  // else the quadrature
   T* yt = (T*)a.yt + (uint64_t)ib * a.t.k * a.t.cpad + c;
-  double* quad = a.scratch + 2 * (a.t.C + a.b.C) + (uint64_t)ib * a.b.C;
   double* out = a.scratch + 2 * (a.t.C + a.b.C) + (uint64_t)a.n_beta * a.b.C;
+  double* quad = col.bath ? out - (uint64_t)(a.n_beta - ib) * a.b.C : out + kTriOut + (uint64_t)ib * a.t.C;
   if (!col.bath && c >= s.C) {
-    for (int i = lane; i < s.k; i += 64) yt[(uint64_t)i * cp] = T(0);
+    if (weights)
+      for (int i = lane; i < s.k; i += 64) yt[(uint64_t)i * cp] = T(0);
     return;
   }
   const double* tmin = a.scratch + (col.bath ? 2 * a.t.C : 0);
@@ -173,7 +177,7 @@ __global__ __launch_bounds__(64) void k_tri_weights(TriArgs a) {
       w[r] = fma(ad[r], t[r], fma(au[r], tu, dn[r] * td));
     }
   };
-  if (half > 0.0) {
+  if (half > 0.0 && z > 1e-17) {
     // Miller's recurrence I_(n-1) = I_(n+1) + (2 n / z) I_n downwards from N
     // terms: e^-z I_N(z) < 1e-20 there, and the start value does not overflow
     const int n_terms = z < 1e-4 ? 6 : z < 1.0 ? 20 : min(a.n_terms(z), a.max_terms);
@@ -210,10 +214,10 @@ __global__ __launch_bounds__(64) void k_tri_weights(TriArgs a) {
     for (int r = 0; r < R; ++r) y[r] *= nrm;
   } else {
 #pragma unroll
-    for (int r = 0; r < R; ++r) y[r] = t0[r];   // T = E0 on every column
+    for (int r = 0; r < R; ++r) y[r] = t0[r];   // T = E0 on every column, or exp(-z (t + 1)) = 1 to rounding
   }
   const double s1 = s.hs[c];
-  if (col.bath) {
+  if (!weights) {
     double q = 0.0;
 #pragma unroll
     for (int r = 0; r < R; ++r) q = fma(y[r], y[r], q);

@@ -36,3 +36,17 @@ def test_many_temperatures_in_one_solve():
         one = rdm.solve(h, inst.betas[b:b + 1], inst.n_v, inst.k, inst.seed, precision="mixed")
         assert np.linalg.norm(got["rho"][b] - one["rho"][0]) < 1e-5 * np.linalg.norm(one["rho"][0])
         assert abs(got["log_z"][b] - one["log_z"][0]) < 1e-5
+
+
+@pytest.mark.parametrize("k,n_beta", [(1, 4), (64, 4), (65, 4), (128, 18), (256, 4), (257, 4)])
+def test_product_quadratures_match_oracle(k, n_beta):
+    # both Hamiltonians' quadratures on the device (one, two and four rows per
+    # lane, two launches' temperatures; the host beyond), temperatures from 0
+    from oracle import product
+    inst = random_dense_terms(2, 6, 960 + k)
+    betas = [0.0, 1e-30, 1e-9] + [0.4 * (i + 1) for i in range(n_beta - 3)]
+    want = product.lanczos_estimate(inst, betas, 3, k, 17)
+    got = rdm.product_trace(rdm.Hamiltonian.from_instance(inst), betas, 3, k, 17, precision="fp64")
+    want["samples"] = want["log_z_t_samples"]
+    for key in ("samples", "log_z", "log_z_t", "log_z_b"):
+        assert np.allclose(got[key], want[key], rtol=1e-10, atol=1e-10), key
