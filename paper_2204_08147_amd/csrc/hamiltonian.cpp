@@ -423,6 +423,7 @@ void free_dev(rdm::OpDevice& d) {
   if (d.dy) (void)hipFree(d.dy);
   if (d.yterms) (void)hipFree(d.yterms);
   if (d.dterms) (void)hipFree(d.dterms);
+  if (d.desc) (void)hipFree(d.desc);
   d = rdm::OpDevice{};
 }
 
@@ -448,6 +449,14 @@ rdm_status get_device_op(const rdm_hamiltonian* h, int which, int precision, hip
     }
   }
   *out = &d;
+  return RDM_OK;
+}
+
+rdm_status apply_desc(const rdm_hamiltonian* h, int which, int precision, Seg** out) {
+  std::lock_guard<std::mutex> lk(h->mu);
+  OpDevice& d = h->dev[which][precision];
+  if (!d.desc) RDM_HIP(hipMalloc((void**)&d.desc, sizeof(Seg)));
+  *out = d.desc;
   return RDM_OK;
 }
 

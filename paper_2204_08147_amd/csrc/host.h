@@ -91,6 +91,7 @@ struct OpDevice {
   void* dy = nullptr;      // D_Y / 2^N, same order (operators with YY couplings)
   void* xterms = nullptr;
   void* yterms = nullptr;
+  Seg* desc = nullptr;     // rdm_apply's segment descriptor (apply_desc)
 };
 
 }  // namespace rdm
@@ -102,6 +103,7 @@ struct rdm_hamiltonian {
   std::vector<double> hx, hz;
   rdm::OpTables op[2];           // [0] H_t, [1] H_b
   mutable std::mutex mu;
+  mutable std::mutex apply_mu;   // held by the rdm_apply call that uses the tables' desc
   mutable rdm::OpDevice dev[2][2];  // [which][precision]
 };
 
@@ -114,6 +116,10 @@ rdm_status get_device_op(const rdm_hamiltonian* h, int which, int precision, hip
 // The same tables if they are already resident on the current device,
 // RDM_E_INVALID otherwise (never builds or allocates).
 rdm_status find_device_op(const rdm_hamiltonian* h, int which, int precision, const OpDevice** out);
+
+// Device memory for one segment descriptor, kept with (which, precision)'s
+// tables; the caller holds h->apply_mu until the device no longer reads it.
+rdm_status apply_desc(const rdm_hamiltonian* h, int which, int precision, Seg** out);
 
 // Symmetric tridiagonal eigenproblem by implicit QR with Wilkinson shifts.
 // Fills theta (n) and zrow = first row of the eigenvector matrix (n), and

@@ -284,6 +284,7 @@ hipError_t launch_small(const Seg* segs, int nseg, int npanels, hipStream_t st);
 // 9 (Y = W_lo T W_lo X^ / 64), 7, 10 (R += W_lo T W_lo Y / 64) after 4-5
 template <typename T>
 hipError_t launch_xz_pass(int pass, const Seg* segs, int nseg, int ntiles, hipStream_t st, int geo = XG_SHALLOW);
+hipError_t launch_put_seg(const Seg& sg, Seg* dst, hipStream_t st);
 // The strided passes of split segments (three launches for one strided pass
 // of the other geometries): op 0: R = W_A R; 1: R = W_B D_X W_B R; 2: Y =
 // W_A Y; 3: Y = W_B D_Y W_B Y; 4: R = L W_A X (X the block Q, L = 4096).

@@ -2231,8 +2231,8 @@ __global__ __launch_bounds__(kBlock) void k_red_alpha(const Seg* __restrict__ se
 // vectors for the whole run -- u_j in LDS (the gathers of the product), u_j,
 // u_{j-1} and r in registers -- and the reductions of a step stay inside it.
 // Launched one kernel per phase, a step of a ten-spin chain is 4 launches of
-// 3-5 us that leave the chip idle; here it is two barriers and two sums, 3.4 us
-// (1 + 9 sites, FP64, 8 columns: 30 steps 470 -> 102 us; with 1024 lanes of one
+// 3-5 us that leave the chip idle; here it is two barriers and two sums, 3.6 us
+// (1 + 9 sites, FP64, 8 columns: 30 steps 470 -> 107 us; with 1024 lanes of one
 // row instead of 256 of four 168 us: the sums and the hops' latency set it).
 // The order of the hops of a row is k_apply's, the rounding order of the
 // recurrence k_norm's and k_apply's and that of the sums the reductions', so
@@ -2674,6 +2674,16 @@ hipError_t launch_xz_split(int op, const Seg* segs, int nseg, int ntiles, hipStr
     case 4: hipLaunchKernelGGL((k_xz_split<T, 4>), g, b, 0, st, segs, nseg); break;
     default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+// One segment descriptor into device memory, from the kernel's arguments (a
+// copy from pageable host memory goes through a staging buffer).
+__global__ __launch_bounds__(64) void k_put_seg(Seg sg, Seg* __restrict__ dst) {
+  if (threadIdx.x == 0) *dst = sg;
+}
+hipError_t launch_put_seg(const Seg& sg, Seg* dst, hipStream_t st) {
+  hipLaunchKernelGGL(k_put_seg, dim3(1), dim3(64), 0, st, sg, dst);
   return hipGetLastError();
 }
 
