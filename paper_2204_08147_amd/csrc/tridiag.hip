@@ -63,7 +63,8 @@ __global__ __launch_bounds__(64) void k_tri_bounds(TriArgs a) {
   bool bad = kk < 1;
   double lo = INFINITY, amin = INFINITY, hi = -INFINITY;
   for (int i = lane; i < s.k; i += 64) {
-    const double x = s.ha[(uint64_t)i * cp + c], y = s.hb[(uint64_t)i * cp + c];
+    // (k - 1 off-diagonals: nothing writes row k - 1 of hb)
+    const double x = s.ha[(uint64_t)i * cp + c], y = i + 1 < s.k ? s.hb[(uint64_t)i * cp + c] : 0.0;
     bad |= !(fabs(x) < INFINITY) || !(fabs(y) < INFINITY);
     if (i < kk) {
       const double bp = i > 0 ? fabs(s.hb[(uint64_t)(i - 1) * cp + c]) : 0.0;

@@ -50,3 +50,22 @@ def test_product_quadratures_match_oracle(k, n_beta):
     want["samples"] = want["log_z_t_samples"]
     for key in ("samples", "log_z", "log_z_t", "log_z_b"):
         assert np.allclose(got[key], want[key], rtol=1e-10, atol=1e-10), key
+
+
+@pytest.mark.parametrize("n_b,apply", [(7, "hops"), (12, "hops"), (15, "transform")])
+@pytest.mark.parametrize("mode", ["stored", "two_pass"])
+def test_no_result_depends_on_the_workspace_content(n_b, apply, mode):
+    # a workspace of NaNs (all bits set) against one of zeros
+    inst = random_dense_terms(1, n_b, 970 + n_b, k=24, betas=(0.5, 2.0), n_v=3)
+    h = rdm.Hamiltonian.from_instance(inst, apply=apply)
+    for precision in ("mixed", "fp64"):
+        opts = dict(precision=precision, mode=mode)
+        ws = torch.empty(rdm.workspace_size(h, len(inst.betas), inst.n_v, inst.k, **opts), dtype=torch.uint8,
+                         device="cuda")
+        got = []
+        for fill in (0, 255):
+            ws.fill_(fill)
+            torch.cuda.synchronize()
+            got.append(rdm.solve(h, inst.betas, inst.n_v, inst.k, inst.seed, workspace=ws, **opts))
+        for key in ("rho", "h_star", "log_z", "entropy"):
+            assert np.array_equal(got[0][key], got[1][key]), (precision, key)
