@@ -6,11 +6,15 @@
 //
 // One wave per column.  The smallest eigenvalue comes from Sturm counts
 // (Givens' bisection) at 64 points at a time, the exponentials from their
-// Chebyshev series on the Gershgorin interval of all columns,
+// Chebyshev series on the column's own interval, from its smallest eigenvalue
+// e to its Gershgorin bound,
 //   exp(-z (t + 1)) = sum_n' 2 (-1)^n e^-z I_n(z) T_n(t),  |t| <= 1,
-// whose coefficients are the modified Bessel functions by Miller's backward
-// recurrence (normalised by e^z = I_0 + 2 sum I_n): every term is a product
-// with the tridiagonal T, one row per lane, so no eigenvectors are formed.
+// times exp(-b (e - E0) / 2): the sum's rounding is 1e-16 of its own largest
+// value, so the weights of a column that lies above E0 (a sector of a conserved
+// quantity) keep their relative accuracy however far above.  Its terms are
+// the modified Bessel functions by Miller's backward recurrence (normalised by
+// e^z = I_0 + 2 sum I_n), each times a product with the tridiagonal T, one row
+// per lane, so no eigenvectors are formed.
 //
 // What bounds it: the latency of these two chains (k x 9 dependent divisions,
 // 41 us at k = 60; 30 + 10 sqrt(z) products, 17-34 us), whatever the number of
@@ -133,15 +137,13 @@ __global__ __launch_bounds__(64) void k_tri_weights(TriArgs a) {
     return;
   }
   const double* tmin = a.scratch + (col.bath ? 2 * a.t.C : 0);
-  double e0 = INFINITY, top = -INFINITY;
+  double e0 = INFINITY;
   bool bad = false;
   for (int i = lane; i < s.C; i += 64) {
     bad |= !(tmin[i] < INFINITY);
     e0 = fmin(e0, tmin[i]);
-    top = fmax(top, tmin[s.C + i]);
   }
   e0 = wave_min(e0);
-  top = wave_max(top);
   bad = __any(bad);
   if (c == 0 && blockIdx.y == 0) {
     int brk = 0;
@@ -153,11 +155,13 @@ __global__ __launch_bounds__(64) void k_tri_weights(TriArgs a) {
     }
   }
   if (bad) return;                         // the host sees the NaN and drops the instance
-  // T = mid + half t with |t| <= 1 on every column's spectrum (a little room
-  // below E0 for its rounding)
-  const double bot = e0 - 1e-14 * fmax(fabs(e0), fabs(top));
+  // T = mid + half t with |t| <= 1 on the column's spectrum (a little room
+  // below its smallest eigenvalue for the rounding of that)
+  const double ec = tmin[c], top = tmin[s.C + c];
+  const double bot = ec - 1e-14 * fmax(fabs(ec), fabs(top));
   const double half = 0.5 * (top - bot), mid = 0.5 * (top + bot);
   const double hb = 0.5 * a.beta[blockIdx.y], z = hb * half;
+  const double low = exp(hb * (e0 - bot));  // exp(-hb (T - E0)) = low exp(-z (t + 1))
   const int kk = s.kc[c];
   double y[R], t0[R], t1[R], ad[R], au[R], dn[R];
 #pragma unroll
@@ -193,7 +197,7 @@ __global__ __launch_bounds__(64) void k_tri_weights(TriArgs a) {
     }
     if (lane == 0) cf[0] = pn;
     __syncthreads();
-    const double nrm = exp(hb * (e0 - bot)) / (pn + 2.0 * sum);
+    const double nrm = 1.0 / (pn + 2.0 * sum);
     product(t0, t1);
 #pragma unroll
     for (int r = 0; r < R; ++r) y[r] = cf[0] * t0[r];
@@ -215,7 +219,7 @@ __global__ __launch_bounds__(64) void k_tri_weights(TriArgs a) {
     for (int r = 0; r < R; ++r) y[r] *= nrm;
   } else {
 #pragma unroll
-    for (int r = 0; r < R; ++r) y[r] = t0[r];   // T = E0 on every column, or exp(-z (t + 1)) = 1 to rounding
+    for (int r = 0; r < R; ++r) y[r] = t0[r];   // a single eigenvalue, or exp(-z (t + 1)) = 1 to rounding
   }
   const double s1 = s.hs[c];
   if (!weights) {
@@ -223,13 +227,13 @@ __global__ __launch_bounds__(64) void k_tri_weights(TriArgs a) {
 #pragma unroll
     for (int r = 0; r < R; ++r) q = fma(y[r], y[r], q);
     q = wave_add(q);
-    if (lane == 0) quad[c] = q / (s1 * s1);
+    if (lane == 0) quad[c] = q * exp(2.0 * hb * (e0 - bot)) / (s1 * s1);  // (low^2 would vanish first)
     return;
   }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int i = lane * R + r;
-    if (i < s.k) yt[(uint64_t)i * cp] = i < kk ? (T)(a.bscale * y[r] * s.hs[(uint64_t)i * cp + c] / s1) : T(0);
+    if (i < s.k) yt[(uint64_t)i * cp] = i < kk ? (T)(a.bscale * (low * y[r]) * s.hs[(uint64_t)i * cp + c] / s1) : T(0);
   }
 }
 
