@@ -315,8 +315,9 @@ rdm_status rdm_start_block(const rdm_hamiltonian* h, int32_t which, int32_t prec
 /* Run only the Lanczos recurrences of a solve (k steps on every start column
  * of H_t, or of H_b if which = 1) and return their coefficients (blocking):
  * host_alpha, host_beta: k x n_cols doubles (row j holds alpha_{j+1} /
- * beta_{j+1} of every column), host_kc: n_cols int32 Krylov sizes after
- * breakdown truncation.  n_cols = d_s*n_v (which = 0) or n_v (which = 1). */
+ * beta_{j+1} of every column; the last beta, which no step computes, is 0),
+ * host_kc: n_cols int32 Krylov sizes after breakdown truncation.
+ * n_cols = d_s*n_v (which = 0) or n_v (which = 1). */
 rdm_status rdm_lanczos(const rdm_hamiltonian* h, int32_t which, int32_t n_v, int32_t k,
                        uint64_t seed, const rdm_options* opt, void* hip_stream,
                        double* host_alpha, double* host_beta, int32_t* host_kc);

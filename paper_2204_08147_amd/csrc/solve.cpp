@@ -266,11 +266,12 @@ struct HostHist {
 rdm_status fetch_hist(const SegPlan& g, char* base, HostHist& hh, hipStream_t st) {
   const size_t n = (size_t)g.k * g.cpad;
   hh.a.resize(n);
-  hh.b.resize(n);
+  hh.b.assign(n, 0.0);  // k steps have k - 1 betas: nothing writes the last row on the device
   hh.s.resize(n);
   hh.kc.resize(g.cpad);
   RDM_HIP(hipMemcpyAsync(hh.a.data(), base + g.o_ha, n * 8, hipMemcpyDeviceToHost, st));
-  RDM_HIP(hipMemcpyAsync(hh.b.data(), base + g.o_hb, n * 8, hipMemcpyDeviceToHost, st));
+  if (g.k > 1)
+    RDM_HIP(hipMemcpyAsync(hh.b.data(), base + g.o_hb, (n - g.cpad) * 8, hipMemcpyDeviceToHost, st));
   RDM_HIP(hipMemcpyAsync(hh.s.data(), base + g.o_hs, n * 8, hipMemcpyDeviceToHost, st));
   RDM_HIP(hipMemcpyAsync(hh.kc.data(), base + g.o_kc, g.cpad * 4, hipMemcpyDeviceToHost, st));
   return RDM_OK;
