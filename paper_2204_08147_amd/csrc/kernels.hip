@@ -886,13 +886,16 @@ __global__ __launch_bounds__(kWideBlock, 4) void k_apply_wide(const Seg* __restr
   {
     const CONST_AS WHop<T>* th = (const CONST_AS WHop<T>*)sg.thin;
     const int nthin = sg.nt0 + sg.nt1 + sg.nt2;
+    const uint32_t B = sg.wbits;
+    // hops that are zero on every row of the tile: no matrix elements there
+    auto vanishes = [&](const WHop<T>& h) {
+      return (h.m & B) == 0u && ((__builtin_popcount(t.base & h.m) & 1u) ? h.cd : h.cs) == T(0);
+    };
     if constexpr (R == Q) {
       WHop<T> h = load_hop<T>(th);
       int i = 0;
-      const uint32_t B = sg.wbits;
-      auto skip = [&]() {              // hops that are zero on every row of the tile: nothing to read
-        while (i < nthin && (h.m & B) == 0u && ((__builtin_popcount(t.base & h.m) & 1u) ? h.cd : h.cs) == T(0))
-          h = load_hop<T>(th + ++i);
+      auto skip = [&]() {              // nothing to read
+        while (i < nthin && vanishes(h)) h = load_hop<T>(th + ++i);
       };
       for (skip(); i < nthin; skip()) {
         const uint32_t rr = lrow ^ h.la;
@@ -913,7 +916,7 @@ __global__ __launch_bounds__(kWideBlock, 4) void k_apply_wide(const Seg* __restr
           for (int r = 0; r < R; ++r) xa[u][r] = ldg(ub, row[r] ^ h[u].la ^ tab[WT_Q + h[u].fq]);
 #pragma unroll
         for (int u = 0; u < kWideAhead; ++u)
-          if (i + u < nthin) hop_part(h[u], xa[u]);
+          if (i + u < nthin && !vanishes(h[u])) hop_part(h[u], xa[u]);   // (0 x would spread an infinite x)
       }
     }
   }
