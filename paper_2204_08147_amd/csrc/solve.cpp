@@ -762,10 +762,13 @@ std::vector<GraphKey> g_graph_order;  // insertion order, for eviction
 std::map<int, hipStream_t> g_graph_stream;
 
 rdm_status graph_steps_locked(int prec, Seg* dsegs, int nseg, const Launch& L, int slab, int cmax, int nsteps,
-                              hipStream_t st, int dev, hipEvent_t t0, hipEvent_t t1);
+                              hipStream_t st, int dev, hipEvent_t t0, hipEvent_t t1,
+                              const std::function<hipError_t()>& beside);
 
+// beside: enqueues work on st that the steps neither read nor write; it runs
+// while they are replayed.
 rdm_status graph_steps(int prec, Seg* dsegs, int nseg, const Launch& L, int slab, int cmax, int nsteps,
-                       hipStream_t st, ReplayTimer* rt) {
+                       hipStream_t st, ReplayTimer* rt, const std::function<hipError_t()>& beside) {
   int dev = 0;
   RDM_HIP(hipGetDevice(&dev));
   // rt: timing events around the replay on the replay stream, read after
@@ -783,7 +786,7 @@ rdm_status graph_steps(int prec, Seg* dsegs, int nseg, const Launch& L, int slab
     if (t0) (void)hipEventDestroy(t0);
     if (t1) (void)hipEventDestroy(t1);
   };
-  rdm_status ls = graph_steps_locked(prec, dsegs, nseg, L, slab, cmax, nsteps, st, dev, t0, t1);
+  rdm_status ls = graph_steps_locked(prec, dsegs, nseg, L, slab, cmax, nsteps, st, dev, t0, t1, beside);
   if (ls == RDM_OK && rt) {
     float ms = 0.f;
     if (hipEventSynchronize(t1) != hipSuccess || hipEventElapsedTime(&ms, t0, t1) != hipSuccess) {
@@ -799,7 +802,8 @@ rdm_status graph_steps(int prec, Seg* dsegs, int nseg, const Launch& L, int slab
 }
 
 rdm_status graph_steps_locked(int prec, Seg* dsegs, int nseg, const Launch& L, int slab, int cmax, int nsteps,
-                              hipStream_t st, int dev, hipEvent_t t0, hipEvent_t t1) {
+                              hipStream_t st, int dev, hipEvent_t t0, hipEvent_t t1,
+                              const std::function<hipError_t()>& beside) {
   std::lock_guard<std::mutex> lk(g_graph_mu);
   hipStream_t gs;
   auto its = g_graph_stream.find(dev);
@@ -850,6 +854,7 @@ rdm_status graph_steps_locked(int prec, Seg* dsegs, int nseg, const Launch& L, i
   if (e == hipSuccess) e = hipGraphLaunch(exec, gs);
   if (e == hipSuccess && t1) e = hipEventRecord(t1, gs);
   if (e == hipSuccess) e = hipEventRecord(after, gs);
+  if (e == hipSuccess) e = beside();
   if (e == hipSuccess) e = hipStreamWaitEvent(st, after, 0);
   (void)hipEventDestroy(before);
   (void)hipEventDestroy(after);
@@ -867,26 +872,35 @@ rdm_status run_phase(std::vector<Seg>& hsegs, Seg* dsegs, int prec, int phase, h
       set_error("internal: a transform segment that needs the Y block has none");
       return RDM_E_INVALID;
     }
-  // small segments run whole, in one launch, from the tail of the table; the
-  // others step together (all of them when the steps are to be timed)
-  const bool small = !tm && !rt;
-  const auto mid = std::stable_partition(hsegs.begin(), hsegs.end(), [&](const Seg& sg) {
-    return !(small && !sg.xz && !sg.wide && sg.nbits <= kSmallBits);
-  });
+  // Small segments run whole, in one launch, from the tail of the table; the
+  // others step together (all of them when the steps are to be timed, or when
+  // larger ones are launched without a graph).  The launch goes beside the
+  // others' replay: in front of it, k steps of a few workgroups hold up the
+  // chip, while as part of it the small segments cost next to nothing unless
+  // they are many (us per call in front / in the steps / beside; k = 50 to 60:
+  // 3 + 11 sites, long range, FP64 5300 / 4340 / 3620; FP32 4370 / 3280 /
+  // 2460; 64 FP64 instances of 11 sites and one of 14 12350 / 15250 /
+  // 11430; one of 11 and eight of 16 to 18, FP32, 11400 / 10900 / 10300).
+  auto is_small = [](const Seg& sg) { return !sg.xz && !sg.wide && sg.nbits <= kSmallBits; };
+  const bool small = !tm && !rt && (graph || std::all_of(hsegs.begin(), hsegs.end(), is_small));
+  const auto mid = std::stable_partition(hsegs.begin(), hsegs.end(),
+                                         [&](const Seg& sg) { return !(small && is_small(sg)); });
   std::vector<Seg> tail(mid, hsegs.end());
   hsegs.erase(mid, hsegs.end());
-  if (!tail.empty()) {
-    Seg* dtail = dsegs + hsegs.size();
+  Seg* const dtail = dsegs + hsegs.size();
+  auto run_tail = [&]() -> hipError_t {
     int panels = 0;
     for (const auto& sg : tail) panels += sg.P;
+    return prec == RDM_FP64 ? launch_small<double>(dtail, (int)tail.size(), panels, st)
+                            : launch_small<float>(dtail, (int)tail.size(), panels, st);
+  };
+  if (!tail.empty())
     RDM_HIP(hipMemcpyAsync(dtail, tail.data(), tail.size() * sizeof(Seg), hipMemcpyHostToDevice, st));
-    RDM_HIP(prec == RDM_FP64 ? launch_small<double>(dtail, (int)tail.size(), panels, st)
-                             : launch_small<float>(dtail, (int)tail.size(), panels, st));
-    if (hsegs.empty()) {
-      // the host table must outlive the asynchronous copy
-      RDM_HIP(hipStreamSynchronize(st));
-      return RDM_OK;
-    }
+  if (hsegs.empty()) {
+    RDM_HIP(run_tail());
+    // the host table must outlive the asynchronous copy
+    RDM_HIP(hipStreamSynchronize(st));
+    return RDM_OK;
   }
   int kmax = 0, cmax = 0;
   for (const auto& sg : hsegs) {
@@ -960,15 +974,17 @@ rdm_status run_phase(std::vector<Seg>& hsegs, Seg* dsegs, int prec, int phase, h
     if (s != RDM_OK) return s;
   }
   if (graph && !tm && kmax - j + 1 >= 2) {
-    rdm_status s = graph_steps(prec, dsegs, nseg, ntiles, slab, cmax, kmax - j + 1, st, rt);
+    rdm_status s = graph_steps(prec, dsegs, nseg, ntiles, slab, cmax, kmax - j + 1, st, rt, run_tail);
     if (s != RDM_OK) return s;
     j = kmax + 1;
+  } else {
+    RDM_HIP(run_tail());
   }
   for (; j <= kmax; ++j) {
     rdm_status s = launch_step(prec, dsegs, nseg, ntiles, slab, cmax, st, tm);
     if (s != RDM_OK) return s;
   }
-  // the host table above must outlive the asynchronous copy
+  // the host tables above must outlive the asynchronous copies
   RDM_HIP(hipStreamSynchronize(st));
   return RDM_OK;
 }

@@ -144,8 +144,9 @@ rdm_status launch_step(int prec, const Seg* dsegs, int nseg, const Launch& L, in
 // low-bit Hadamard basis (xz_tiles tiles from tile xz_boff).
 rdm_status init_run(int prec, const Seg* dsegs, int nseg, int cmax, int phase, int xz_tiles, int xz_boff,
                     hipStream_t st);
-// Small hop-table segments (kSmallBits) run in a launch of their own and leave
-// hsegs, unless the steps are timed (tm, rt).
+// Small hop-table segments (kSmallBits) run in a launch of their own beside the
+// others' replay and leave hsegs, unless the steps are timed (tm, rt) or
+// larger segments run without a graph.
 rdm_status run_phase(std::vector<Seg>& hsegs, Seg* dsegs, int prec, int phase, hipStream_t st,
                      StepTimers* tm, bool tune, bool graph, ReplayTimer* rt = nullptr);
 // Panels per lane for a launch over these segments: the cached measurement
