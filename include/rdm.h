@@ -167,9 +167,9 @@ rdm_status rdm_hamiltonian_create(int32_t n_s, int32_t n_b, const rdm_coupling* 
  *     T = diag((-1)^floor(popcount(idx)/2)), D_Y), streamed in tiles;
  *     other sizes use hop tables;
  *   RDM_APPLY_AUTO (what rdm_hamiltonian_create does): the transform where
- *     available, unless a hop table would read fewer partner rows per row
- *     than the transform streams vectors (sparse operators with YY terms);
- *     hop tables as under RDM_APPLY_HOPS otherwise.
+ *     available, but hop tables as under RDM_APPLY_HOPS for operators with
+ *     YY terms or above 22 sites that read fewer than 40 partner rows per
+ *     row on 256-row tiles (sparse ones).
  * rdm_hamiltonian_info reports the choice for H_t and H_b.  RDM_E_INVALID
  * for another value of apply. */
 rdm_status rdm_hamiltonian_create_ex(int32_t n_s, int32_t n_b, const rdm_coupling* couplings,

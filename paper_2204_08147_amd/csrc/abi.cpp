@@ -479,9 +479,10 @@ extern "C" rdm_status rdm_apply(const rdm_hamiltonian* h, int32_t which, int32_t
   sg = one[0];
   // The segment descriptor lives with the operator's tables, a second call at
   // the same time allocates its own; a kernel with the descriptor as argument
-  // writes it (with an allocation, a copy and a free per call a product on 21
-  // sites x 24 columns took 254 us, now 249, of which 237 are its passes; 40
-  // hops on 20 sites x 13 FP64 columns 158 and 143).  The scratch block of a YY transform part is given back on return.
+  // writes it (with an allocation, a copy and a free per call 40 hops on 20
+  // sites x 13 FP64 columns took 158 us, now 143; a product on 21 sites x 24
+  // columns, 237 us of passes, takes 251 either way).  The scratch block of a
+  // YY transform part is given back on return.
   std::unique_lock<std::mutex> own(h->apply_mu, std::try_to_lock);
   Seg* d = nullptr;
   char* extra = nullptr;

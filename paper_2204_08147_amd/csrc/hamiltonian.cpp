@@ -224,15 +224,19 @@ void compile(const rdm_hamiltonian& h, int first_site, OpTables& t) {
   any_x = !xt.empty();
   any_y = !yt.empty();
   const bool in_range = t.nbits >= kXzMinBits && t.nbits <= kXzMaxBits && (any_x || any_y);
-  // A transform step streams 8 vectors, 15 with a YY part and 4 more with
-  // split strided passes (above 22 bits); a hop-table step streams about 6
-  // and reads one partner row per staged partner tile and per gathered hop,
-  // from cache for the most part.  Measured: with YY terms the hop tables win
-  // at 28 partner rows per row (random graphs of degree 4, 22 bits) and lose
-  // from 78 on (all pairs, 20-26 bits); with split passes the transverse-field
-  // chain (16 partner rows) runs 3-4 % faster from hop tables.  So operators
-  // with YY terms, and all operators above 22 bits, take the transform from
-  // 40 partner rows on; X-type operators up to 22 bits always.
+  // A transform step streams 8 vectors, with a YY part 13 in FP32 and 15 in
+  // FP64, and 4 (8 with YY) more with split strided passes (above 22 bits); a
+  // hop-table step streams about 6 and reads one partner row per staged partner
+  // tile and per gathered hop, from cache for the most part.  Operators with YY
+  // terms, and all operators above 22 bits, take the transform from 40 partner
+  // rows on; X-type operators up to 22 bits always.  The line was drawn with
+  // the hop tables' 256-row tiles.  On bit-set tiles it lies too low, most of
+  // all in FP64 (random XXZ graphs, 16 columns, ms per step from hop tables /
+  // the transform, by partner rows): 20 sites FP32 40 rows 0.181 / 0.243, 54
+  // 0.228 / 0.243, 68 0.263 / 0.243; FP64 40 0.307 / 0.467, 68 0.462 / 0.467,
+  // 78 0.489 / 0.464; 22 sites FP32 41 0.775 / 0.989, 58 0.901 / 1.026, 69
+  // 0.996 / 0.977, 105 1.31 / 0.95; FP64 41 1.50 / 2.30, 85 2.19 / 2.31, 105
+  // 2.60 / 2.31; 23 sites FP32 46 1.48 / 2.48, 92 2.50 / 2.46, 120 3.21 / 2.47.
   const int partners = (int)(t.groups.size() - 1 + thin[0].size() + thin[1].size() + thin[2].size());
   const bool dense_enough = partners >= 40;
   bool use = false;

@@ -331,7 +331,7 @@ constexpr int kTriRows = 4;                  // rows of T per lane at most
 constexpr int kTriMaxK = 64 * kTriRows;
 constexpr int kTriBetas = 16;                // temperatures per launch
 constexpr int kTriMaxTerms = 4000;
-constexpr int kTriMaxBits = 20;
+constexpr int kTriMaxBits = 20;              // (tri_in_range says why)
 // Lanczos coefficients of one segment ([k][cpad]) and its Krylov sizes
 struct TriSeg {
   const double *ha, *hb, *hs;
@@ -351,7 +351,11 @@ struct TriArgs {
   double bscale;                             // factor of the weights
   int32_t n_beta, beta0, max_terms;
   double beta[kTriBetas];
-  // terms of exp(-z (t + 1)) for z >= 1: e^-z I_n(z) < e^(-n^2 / 2z) < e^-50
+  // terms of exp(-z (t + 1)) for z >= 1: ln(e^-z I_n(z)) <= sqrt(n^2 + z^2) - z
+  // - n asinh(n / z) (Chernoff's bound on the difference of two Poisson
+  // variables of mean z / 2, which has n with probability e^-z I_n(z)): at
+  // this n at most -50.7 for 1 <= z <= 1.6e5 (kTriMaxTerms); -54 and -64 at
+  // the 20 and 6 terms that smaller z take
   __host__ __device__ static int n_terms(double z) { return 30 + (int)(10.0 * sqrt(z)); }
 };
 template <typename T>

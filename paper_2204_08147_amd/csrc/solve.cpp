@@ -585,8 +585,13 @@ double norm_bound(const OpTables& t) {
 bool tri_in_range(const rdm_hamiltonian* h, int k, double beta_max, double* zmax) {
   // half the width of T's Gershgorin interval is at most 2 |H|, so z =
   // (beta / 2) * that is at most beta |H| (FP32 recurrences: to rounding).
-  // Above 2^kTriMaxBits rows the host takes less than 1 % of a solve: 36
-  // columns on 23 bits 0.5 ms of 690.
+  // Above 2^kTriMaxBits rows the host keeps the weights by choice, not for
+  // speed: in mixed precision the two forms round some FP32 weights
+  // differently, which moves H* there by 1e-12 to 4e-10 (16 instances of 3 +
+  // 20 sites; both are 2e-7 to 3e-7 from the FP64 solve), and results of large
+  // solves stay what they were.  It costs 0.3 to 1.2 ms a solve: 7.87 against
+  // 7.58 ms (21 sites, 2 columns, 4 temperatures), 58.9 / 57.8 (21 sites, 64
+  // columns), 28.1 / 27.8 (23 sites, 2 columns), 161.6 / 160.5 (32 columns).
   *zmax = std::max(1.0, 1.01 * beta_max * std::max(norm_bound(h->op[0]), norm_bound(h->op[1])));
   return h->n <= kTriMaxBits && k <= kTriMaxK && *zmax < 1e8 && TriArgs::n_terms(*zmax) <= kTriMaxTerms;
 }

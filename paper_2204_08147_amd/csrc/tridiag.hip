@@ -17,8 +17,8 @@
 // per lane, so no eigenvectors are formed.
 //
 // What bounds it: the latency of these two chains (k x 9 dependent divisions,
-// 41 us at k = 60; 30 + 10 sqrt(z) products, 17-34 us), whatever the number of
-// columns up to the chip's waves.  On 16 host threads (implicit QR per column,
+// 21 us at k = 30, 35-41 at 60; 30 + 10 sqrt(z) products, 9-32 us), whatever
+// the number of columns up to the chip's waves.  On 16 host threads (implicit QR per column,
 // coefficients copied to the host and weights back) 3 x 500 columns with
 // 8 temperatures took 25 ms of a solve, now 0.25 ms; 80 columns with
 // 4 temperatures 1.6 ms, now 0.06 ms; 12 columns with k = 30 0.3 ms, now 0.04;
@@ -184,7 +184,7 @@ __global__ __launch_bounds__(64) void k_tri_weights(TriArgs a) {
   };
   if (half > 0.0 && z > 1e-17) {
     // Miller's recurrence I_(n-1) = I_(n+1) + (2 n / z) I_n downwards from N
-    // terms: e^-z I_N(z) < 1e-20 there, and the start value does not overflow
+    // terms: e^-z I_N(z) < 1e-21 there, and the start value does not overflow
     const int n_terms = z < 1e-4 ? 6 : z < 1.0 ? 20 : min(a.n_terms(z), a.max_terms);
     double pn1 = 0.0, pn = 1e-300, sum = 0.0;
     const double tz = 2.0 / z;
