@@ -859,8 +859,11 @@ rdm_status graph_steps_locked(int prec, Seg* dsegs, int nseg, const Launch& L, i
   if (e == hipSuccess) e = hipGraphLaunch(exec, gs);
   if (e == hipSuccess && t1) e = hipEventRecord(t1, gs);
   if (e == hipSuccess) e = hipEventRecord(after, gs);
-  if (e == hipSuccess) e = beside();
-  if (e == hipSuccess) e = hipStreamWaitEvent(st, after, 0);
+  if (e == hipSuccess) {
+    const hipError_t eb = beside();
+    e = hipStreamWaitEvent(st, after, 0);  // also when that launch failed: the replay is under way
+    if (e == hipSuccess) e = eb;
+  }
   (void)hipEventDestroy(before);
   (void)hipEventDestroy(after);
   RDM_HIP(e);
